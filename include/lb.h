@@ -153,10 +153,12 @@ int lb_step(lb_lattice *lat, int n);
  * steps as lb_step, with the same results (state and totals bit for bit), but
  * the call allocates nothing.  The totals' scratch (the reduce's arrival
  * ticket and the per-workgroup FP64 partials) lives in a file-scope device
- * array of the library, 8 MiB + 64 KiB per device, held until the process
+ * array of the library, 16 MiB + 128 KiB per device, held until the process
  * ends; each step is an ordinary kernel launch on the lattice stream (no
  * graph is built, so a caller may capture the call into its own).
- * Limit: 64 bytes per step workgroup plus 256 + 32 per 256 workgroups; a
+ * Limit: 64 bytes per step workgroup plus 256 + 64 per 256 workgroups, in
+ * half of the array; lattices whose totals are split (FP32 without solids,
+ * where two-step launches pay) take twice of both; a
  * 512^3 lattice at 4 sites per lane (131072 workgroups) fits, lattices that
  * need more are rejected with LB_EINVAL and the sizes in lb_last_error().  All calls on one device
  * share the one array, which keeps the last call's contents: calls that
@@ -246,7 +248,9 @@ long long lb_steps_done(const lb_lattice *lat);
  * codec, 10 = range widenings of LB_S16 storage so far, 11 = tile order (0
  * linear, 1 a contiguous range of tiles per XCD, 2 linear with each block of
  * 64 tiles rotated by its index), 12 = 1 if the steps of a
- * lattice with solids pull with non-temporal loads (else cached loads).
+ * lattice with solids pull with non-temporal loads (else cached loads), 13 =
+ * steps that one launch of a run takes (2 for FP32 lattices without solids
+ * where the launch shape pays, as long as no force field is set; else 1).
  * Returns -1 for an unknown key or a bad handle.
  */
 long long lb_query(const lb_lattice *lat, int key);

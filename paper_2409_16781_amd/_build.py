@@ -11,6 +11,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "liblbm355.so")
 SOURCES = [os.path.join(CSRC, n) for n in ("lb_capi.hip", "lb_batch.hip", "lb_d2q9.hip", "lb_kernels.hip",
                                            "lb_batch_kernels.hip", "lb_adjoint_kernels.hip", "lb_aa_kernels.hip",
+                                           "lb_march_kernels.hip",
                                            "lb_d2q9_kernels.hip")]
 
 # -packed-fp32-ops: no packed FP32 instructions in device code (ordinary FP32

@@ -29,7 +29,7 @@ __device__ __forceinline__ void collide_lane(Lane<NW> (&d)[kQ], const Coll &cp)
     float mr[V], mu[V], mv[V], mw[V], fxs[V];
     Range16 rng;
     const Scale16 sc{};
-    collide_sites<C, NW, false>(d, cp, sc, rng, fxs, mr, mu, mv, mw);
+    collide_sites<C, NW, 0>(d, cp, sc, rng, fxs, mr, mu, mv, mw);
 }
 
 // Wave budget of the in-place kernels: that of the two-array step (the same
@@ -58,15 +58,22 @@ __device__ __forceinline__ uint32_t own_masks(const StepArgs &a, const TileGeom 
 }
 
 // Odd -> even: read, collide, write swapped, all at the site itself.
-template <int C, int NW, bool kSolids>
+template <int C, int NW, bool kSolids, int NC>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(aa_waves<C, NW>()))) void aa_local(StepArgs a)
 {
     using K = Codec<C>;
     constexpr int V = NW * 4 / K::kBytes;
+    int b = blockIdx.x;
+    if (a.prev_own && b-- == 0) {
+        append_prev_totals<NC>(a.nprev, a.prev);
+        return;
+    }
     char *F = reinterpret_cast<char *>(a.dst);
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    double acc[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) acc[k] = 0.0;
     const int ntiles = (a.nslots + kBlock - 1) / kBlock;
-    if (const int b = blockIdx.x; b < ntiles) {  // one workgroup per tile
+    if (b < ntiles) {  // one workgroup per tile
         const TileGeom g = tile_geom<V, false>(a, tile_of(b, ntiles, a.tile_order));
         Lane<NW> d[kQ];
 #pragma unroll
@@ -96,10 +103,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(aa_waves
                             if (!((dead >> e) & 1u)) st_elem<C>(F, g.own + OPP[i] * a.lay.seg + e, vget<C, NW>(d[i], e));
                 }
             }
-            add_lane_totals<C, NW>(d, acc, a.sc);
+            add_lane_totals<C, NW, NC>(d, acc, a.sc, a.split);
         }
     }
-    store_block_totals(acc, a.partials + 4 * (size_t)blockIdx.x);
+    store_block_totals<NC>(acc, a.partials + NC * (size_t)b);
+    if (a.nprev > 0 && !a.prev_own && b == 0) append_prev_totals<NC>(a.nprev, a.prev);
 }
 
 // Even -> odd: gather (transposed slots), collide, push to the neighbours.
@@ -114,7 +122,7 @@ constexpr int push_waves()
     return (C == kF16 && NW <= 2) ? 2 : aa_waves<C, NW>();
 }
 
-template <int C, int NW, bool kSolids>
+template <int C, int NW, bool kSolids, int NC>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(push_waves<C, NW>()))) void aa_pullpush(StepArgs a)
 {
     using K = Codec<C>;
@@ -122,14 +130,21 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(push_wav
     constexpr uint32_t kAll = (1u << V) - 1u;
     __shared__ EdgeLds lds;
     __shared__ uint32_t dead_row_last[kBlock], dead_row_first[kBlock], dead_wave_last[4], dead_wave_first[4];
+    int b = blockIdx.x;
+    if (a.prev_own && b-- == 0) {
+        append_prev_totals<NC>(a.nprev, a.prev);
+        return;
+    }
     char *F = reinterpret_cast<char *>(a.dst);
     const uint32_t nx = (uint32_t)a.nx, ny = (uint32_t)a.ny, nz = (uint32_t)a.nz;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    double acc[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) acc[k] = 0.0;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int rit = (int)threadIdx.x >> a.lg_row_lanes;
     const int ntiles = (a.nslots + kBlock - 1) / kBlock;
-    if (const int b = blockIdx.x; b < ntiles) {  // one workgroup per tile
+    if (b < ntiles) {  // one workgroup per tile
         const TileGeom g = tile_geom<V, false>(a, tile_of(b, ntiles, a.tile_order));
         Lane<NW> d[kQ];
         const uint32_t dead = gather<C, NW, kSolids, false, true>(a, F, g, d, lds);
@@ -145,7 +160,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(push_wav
                 }
         }
         if (g.active) {
-            add_lane_totals<C, NW>(d, acc, a.sc);
+            add_lane_totals<C, NW, NC>(d, acc, a.sc, a.split);
             // bounce-back: where x + c_i is solid (bit opp(i)), f*_i(x) stays at x, in slot opp(i)
             if constexpr (kSolids) {
 #pragma unroll
@@ -236,26 +251,29 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(push_wav
         }
         (void)nz;
     }
-    store_block_totals(acc, a.partials + 4 * (size_t)blockIdx.x);
+    store_block_totals<NC>(acc, a.partials + NC * (size_t)b);
+    if (a.nprev > 0 && !a.prev_own && b == 0) append_prev_totals<NC>(a.nprev, a.prev);
 }
 
 }  // namespace
 
 namespace {
-template <int C, int NW, bool S>
+template <int C, int NW, bool S, int NC>
 void *aa_fn(bool from_even)
 {
-    return from_even ? reinterpret_cast<void *>(&aa_pullpush<C, NW, S>) : reinterpret_cast<void *>(&aa_local<C, NW, S>);
+    return from_even ? reinterpret_cast<void *>(&aa_pullpush<C, NW, S, NC>)
+                     : reinterpret_cast<void *>(&aa_local<C, NW, S, NC>);
 }
-template <int C, bool S>
+template <int C, bool S, int NC = 4>
 void *aa_pick_nw(int variant, bool from_even)
 {
-    if (variant == 1) return aa_fn<C, 4, S>(from_even);
-    if (variant == 2) return aa_fn<C, 2, S>(from_even);
-    return aa_fn<C, 1, S>(from_even);
+    if (variant == 1) return aa_fn<C, 4, S, NC>(from_even);
+    if (variant == 2) return aa_fn<C, 2, S, NC>(from_even);
+    return aa_fn<C, 1, S, NC>(from_even);
 }
-void *pick_aa(int codec, int variant, bool solids, bool from_even)
+void *pick_aa(int codec, int variant, bool solids, bool split, bool from_even)
 {
+    if (split) return aa_pick_nw<kF32, false, 8>(variant, from_even);
     switch (codec) {
         case kF32: return solids ? aa_pick_nw<kF32, true>(variant, from_even) : aa_pick_nw<kF32, false>(variant, from_even);
         case kF16: return solids ? aa_pick_nw<kF16, true>(variant, from_even) : aa_pick_nw<kF16, false>(variant, from_even);
@@ -268,14 +286,15 @@ hipError_t launch_aa_step(int codec, int variant, bool solids, bool from_even, c
                           hipStream_t s)
 {
     StepArgs arg = a;
+    arg.prev_own = prev_own_group(a, grid);
     void *params[] = {&arg};
-    return hipLaunchKernel(pick_aa(codec, variant, solids, from_even), dim3(grid), dim3(kBlock), params, 0, s);
+    return hipLaunchKernel(pick_aa(codec, variant, solids, a.split.m1 != 0.0, from_even), dim3(grid + arg.prev_own), dim3(kBlock), params, 0, s);
 }
 
 int aa_occupancy(int codec, int variant, bool solids, bool from_even)
 {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, pick_aa(codec, variant, solids, from_even), kBlock, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, pick_aa(codec, variant, solids, false, from_even), kBlock, 0) !=
         hipSuccess)
         return 1;
     return nb < 1 ? 1 : nb;

@@ -22,7 +22,7 @@ __device__ __forceinline__ void append_batch_totals(const BatchTotalsArgs &t)
     for (int d = (int)threadIdx.x >> 6; d < t.ndoms; d += kBlock / 64) {
         const DomDesc &D = t.doms[d];
         double tot[4];
-        wave_sum4(t.partials + 4 * (size_t)D.tile_begin, D.ntiles, tot);
+        wave_sum<4>(t.partials + 4 * (size_t)D.tile_begin, D.ntiles, tot);
         if ((threadIdx.x & 63) == 0) {
             double *r = t.ring + 4 * ((size_t)d * kRingCap + step % kRingCap);
             r[0] = D.n_fluid + tot[0];
@@ -46,8 +46,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(vec_wave
         const char *src = reinterpret_cast<const char *>(D.buf[a.parity]);
         char *dst = reinterpret_cast<char *>(D.buf[a.parity ^ 1]);
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        tile_update<C, NW, true, false, true>(s, src, dst, t - D.tile_begin, acc, lds);
-        store_block_totals(acc, a.partials + 4 * (size_t)t);
+        tile_update<C, NW, true, false, true, 4>(s, src, dst, t - D.tile_begin, acc, lds);
+        store_block_totals<4>(acc, a.partials + 4 * (size_t)t);
         __syncthreads();  // the totals' LDS is reused by the next tile
     }
     if (a.prev.partials != nullptr && blockIdx.x == 0) append_batch_totals(a.prev);
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kBlock) void reduce_domains(BatchTotalsArgs a)
     const int d = blockIdx.x;
     const unsigned long long step = __hip_atomic_load(a.step_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     double tot[4];
-    block_sum4(a.partials + 4 * (size_t)a.doms[d].tile_begin, a.doms[d].ntiles, tot, false);
+    block_sum<4>(a.partials + 4 * (size_t)a.doms[d].tile_begin, a.doms[d].ntiles, tot, false);
     if (threadIdx.x == 0) {
         double *r = a.ring + 4 * ((size_t)d * kRingCap + step % kRingCap);
         r[0] = a.doms[d].n_fluid + tot[0];

@@ -29,7 +29,7 @@ using namespace lbm;
 // file-scope device array instead of the lattice's own allocations.  Every
 // device holds its own copy at its own address; host code uses only that
 // address (scratch_base), never the array's name.
-constexpr size_t kScratchBytes = ((size_t)8 << 20) + ((size_t)64 << 10);  // 8 MiB + 64 KiB
+constexpr size_t kScratchBytes = ((size_t)16 << 20) + ((size_t)128 << 10);  // 16 MiB + 128 KiB
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace lbm {
@@ -90,6 +90,7 @@ struct lb_lattice {
     double n_fluid;
     double *partials;
     double *gpartials;
+    TotalSplit split;  // of split totals (total_split), or zeros
     unsigned int *ticket;
     double *ring;
     unsigned long long *counter;
@@ -97,6 +98,7 @@ struct lb_lattice {
     int variant, vsites, grid, cus;
     int tile_order;
     int pull_nt;      // 1: plain steps with solids pull with non-temporal loads
+    MarchShape march; // two-step launches (march.use: runs of plain steps take them)
     bool inplace;     // one population array (AA pattern); cur is then the phase (0 even, 1 odd)
     long long steps;
     RunGraphs graphs;
@@ -156,6 +158,7 @@ StepArgs step_args(const lb_lattice *h, int from, float *rho, float *u, int vari
     a.rho_out = rho;
     a.u_out = u;
     a.partials = h->partials;
+    a.split = h->split;
     a.fx_field = h->ffield;
     a.sc = h->sc;
     a.ovf = h->ovf;
@@ -185,16 +188,19 @@ MacroArgs macro_args(const lb_lattice *h, int cur, float *rho, float *u)
     return a;
 }
 
-// Device buffers of the per-step totals: the step workgroups' partials (two
-// buffers of grid slots, for runs of steps), the reduce workgroups' partials
-// and the reduce's arrival ticket.
+// Device buffers of the per-step totals: the launches' partials (two buffers
+// of parts slots, for runs of steps), the reduce workgroups' partials and the
+// reduce's arrival ticket.
 struct TotalsBufs {
+    size_t parts;
     double *partials;
     double *gpartials;
     unsigned int *ticket;
 };
 
-TotalsBufs own_bufs(const lb_lattice *h) { return TotalsBufs{h->partials, h->gpartials, h->ticket}; }
+size_t buf_parts(const lb_lattice *h);
+
+TotalsBufs own_bufs(const lb_lattice *h) { return TotalsBufs{buf_parts(h), h->partials, h->gpartials, h->ticket}; }
 
 // ---- the scratch array's address per device (resolved once per device, with
 // that device current, when the first lattice is created on it)
@@ -221,37 +227,67 @@ unsigned char *scratch_base(int dev)
     return (dev >= 0 && dev < kMaxDevices) ? g_scratch_base[dev] : nullptr;
 }
 
-// Scratch layout for lattice h: ticket (one 256-byte slot), the reduce
-// workgroups' partials (4 doubles each, rounded up to 256 bytes), then two
-// buffers of 4 doubles per step workgroup.
-size_t scratch_gpart_bytes(const lb_lattice *h)
+// Doubles of one workgroup's totals in the current kernel of h, and the most
+// that any kernel of h writes (a force field may come and go).
+int total_parts_of(const lb_lattice *h)
 {
-    const size_t ngroups = ((size_t)h->grid + kRedChunk - 1) / kRedChunk;
-    return (ngroups * 4 * sizeof(double) + 255) & ~(size_t)255;
+    return h->split.m1 != 0.0 && !h->ffield && h->variant != 0 ? 8 : 4;
 }
 
-size_t scratch_need(const lb_lattice *h)
+int max_total_parts(const lb_lattice *h) { return h->split.m1 != 0.0 ? 8 : 4; }
+
+// Scratch layout for lattice h and runs of parts partials per buffer: ticket
+// (one 256-byte slot), the reduce workgroups' partials (4 doubles each, split totals: 8; rounded up to 256 bytes),
+// then two buffers of as many doubles per partial.
+size_t scratch_gpart_bytes(const lb_lattice *h, size_t parts)
 {
-    return 256 + scratch_gpart_bytes(h) + (size_t)h->grid * 8 * sizeof(double);
+    const size_t ngroups = (parts + kRedChunk - 1) / kRedChunk;
+    return (ngroups * 2 * max_total_parts(h) * sizeof(double) + 255) & ~(size_t)255;
 }
 
-TotalsBufs scratch_bufs(const lb_lattice *h, unsigned char *base)
+size_t scratch_need(const lb_lattice *h, size_t parts)
+{
+    return 256 + scratch_gpart_bytes(h, parts) + parts * 2 * max_total_parts(h) * sizeof(double);
+}
+
+// Bytes of the array that a lattice may use: the same number of step
+// workgroups for every kind (split totals take twice the space).
+size_t scratch_limit(const lb_lattice *h) { return kScratchBytes / 8 * max_total_parts(h); }
+
+TotalsBufs scratch_bufs(const lb_lattice *h, unsigned char *base, size_t parts)
 {
     TotalsBufs tb;
+    tb.parts = parts;
     tb.ticket = reinterpret_cast<unsigned int *>(base);
     tb.gpartials = reinterpret_cast<double *>(base + 256);
-    tb.partials = reinterpret_cast<double *>(base + 256 + scratch_gpart_bytes(h));
+    tb.partials = reinterpret_cast<double *>(base + 256 + scratch_gpart_bytes(h, parts));
     return tb;
 }
 
-// Totals of the step whose workgroup partials are in buffer buf (0 or 1) and
-// whose source array is buf[par] (its overflow flag, for scaled storage).
-TotalsArgs totals_args(const lb_lattice *h, int buf, const TotalsBufs &tb, int par)
+// The partials (one per tile and plane) of each step of a two-step launch, the
+// partials that one buffer of a run holds, and whether runs with the buffers
+// tb take two steps per launch.
+int march_parts(const lb_lattice *h) { return h->march.nxt * h->march.nyt * h->nz; }
+
+size_t buf_parts(const lb_lattice *h)
+{
+    return std::max((size_t)h->grid, h->march.use ? 2 * (size_t)march_parts(h) : (size_t)0);
+}
+
+bool run_pairs(const lb_lattice *h, const TotalsBufs &tb)
+{
+    return h->march.use && !h->ffield && h->variant != 0 && tb.parts >= 2 * (size_t)march_parts(h);
+}
+
+// Totals of a step whose nparts partials start at partials and whose source
+// array is buf[par] (its overflow flag, for scaled storage).
+TotalsArgs totals_args(const lb_lattice *h, const double *partials, int nparts, const TotalsBufs &tb, int par)
 {
     TotalsArgs t{};
     t.ovf = h->codec == kS16 ? h->ovf + par : nullptr;
-    t.partials = tb.partials + (size_t)buf * 4 * h->grid;
-    t.nparts = h->grid;
+    t.nc = total_parts_of(h);
+    t.partials = partials;
+    t.nparts = nparts;
     t.gpartials = tb.gpartials;
     t.ticket = tb.ticket;
     t.ring = h->ring;
@@ -288,12 +324,41 @@ constexpr int kS16MaxExp = 60;  // narrowest range: |g| < 2^-45
 
 int enqueue_steps(lb_lattice *h, int n, float *rho, float *u);
 
-// count steps from buf[from] as one run with chained totals.  path (count + 1
-// arrays, or NULL for the A/B pair): step k reads path[k] and writes
-// path[k + 1].  mom (count pointers, or NULL): step k also writes its moments
-// (one record rho, u_x, u_y, u_z per site, site order) to mom[k].
-int enqueue_run(lb_lattice *h, int from, int count, hipStream_t s, const TotalsBufs &tb, void *const *path = nullptr,
-                float *const *mom = nullptr);
+// Arguments of a two-step launch of h (the caller sets the arrays).
+MarchArgs march_args(const lb_lattice *h)
+{
+    MarchArgs a{};
+    a.lay = h->lay;
+    a.nx = h->nx;
+    a.ny = h->ny;
+    a.nz = h->nz;
+    a.nxt = h->march.nxt;
+    a.nzt = h->march.nzt;
+    a.ntiles = h->march.nxt * h->march.nyt * h->march.nzt;
+    a.rows = h->march.rows;
+    a.chunk = h->march.chunk;
+    a.coll = make_coll((float)h->omega, (float)h->force[0], (float)h->force[1], (float)h->force[2]);
+    a.split = h->split;
+    return a;
+}
+
+// Where a run reads and writes instead of the A/B pair: it starts from
+// start, its last launch writes end (nullptr: that state is not kept), the
+// launches in between go through tmp[0] and tmp[1] in turn.
+struct RunPath {
+    const void *start;
+    void *end;
+    void *tmp[2];
+};
+
+// count steps from buf[from] as one run with chained totals.  path: see
+// above, or NULL for the A/B pair.  mom (count pointers, or NULL): step k also
+// writes its moments (one record rho, u_x, u_y, u_z per site, site order) to
+// mom[k].  rho, u: the last step also writes its density and velocity (one
+// or two-step launches of the row kernels).  totals = false: no totals are
+// appended to the ring.
+int enqueue_run(lb_lattice *h, int from, int count, hipStream_t s, const TotalsBufs &tb, const RunPath *path = nullptr,
+                float *const *mom = nullptr, float *rho = nullptr, float *u = nullptr, bool totals = true);
 
 // Wait for the lattice's work; if a scaled-storage step overflowed, widen
 // the range of each weight class whose codes left it by one bit
@@ -354,46 +419,94 @@ int enqueue_one(lb_lattice *h, int from, float *rho, float *u, hipStream_t s, co
     a.partials = tb.partials;
     if (h->inplace) {
         HIP_OR_FAIL(launch_aa_step(h->codec, h->variant, h->solids, from == 0, a, h->grid, s));
-        HIP_OR_FAIL(launch_totals(totals_args(h, 0, tb, from), s));
+        const TotalsArgs t = totals_args(h, tb.partials, h->grid, tb, from);
+        HIP_OR_FAIL(launch_totals(&t, 1, s));
         if (macros) HIP_OR_FAIL(launch_macros(h->codec, macro_args(h, from ^ 1, rho, u), s));
         return LB_OK;
     }
     HIP_OR_FAIL(launch_step(h->codec, h->variant, h->solids, macros, a, h->grid, s));
-    HIP_OR_FAIL(launch_totals(totals_args(h, 0, tb, from), s));
+    const TotalsArgs t = totals_args(h, tb.partials, h->grid, tb, from);
+    HIP_OR_FAIL(launch_totals(&t, 1, s));
     if (macros && h->solids && h->variant == 0)
         HIP_OR_FAIL(launch_zero_solid_macros(h->flags, (int)h->n, rho, u, s));
     return LB_OK;
 }
 
-// Enqueue count >= 1 steps without macros from buf[from] on stream s.  On
-// the vector-row kernels the steps form a run: step k writes its workgroup
-// partials into buffer k & 1, the first workgroup of step k + 1 appends the
-// totals of step k, and one totals kernel closes the run.  The ring then
-// holds the same values as with a totals kernel after every step.
-int enqueue_run(lb_lattice *h, int from, int count, hipStream_t s, const TotalsBufs &tb, void *const *path,
-                float *const *mom)
+// Enqueue count >= 1 steps without macros from buf[from] on stream s (they
+// end in buf[run_end]).  On the vector-row kernels the steps form a run: a
+// launch writes its partials into one of two buffers in turn, a workgroup of
+// the next launch appends their totals, and one totals kernel closes the run.
+// The ring then holds the same values as with a totals kernel after every
+// step.
+int enqueue_run(lb_lattice *h, int from, int count, hipStream_t s, const TotalsBufs &tb, const RunPath *path,
+                float *const *mom, float *rho, float *u, bool totals)
 {
-    if (h->inplace || h->variant == 0) {
-        if (path || mom) return fail(LB_EINVAL, "explicit step buffers need the two-array row kernels");
+    if ((h->inplace || h->variant == 0) && (path || mom || rho || !totals))
+        return fail(LB_EINVAL, "explicit step buffers need the two-array row kernels");
+    if (h->variant == 0) {
         for (int k = 0; k < count; ++k) {
             int rc = enqueue_one(h, from ^ (k & 1), nullptr, nullptr, s, tb);
             if (rc) return rc;
         }
         return LB_OK;
     }
-    for (int k = 0; k < count; ++k) {
-        StepArgs a = step_args(h, from ^ (k & 1), mom ? mom[k] : nullptr, nullptr);
-        a.mom_rec = mom ? 1 : 0;
-        if (path) {
-            a.src = path[k];
-            a.dst = path[k + 1];
+    // Each launch takes one step or, where that is faster, two; it writes its
+    // steps' partials into one of the two buffers in turn, and a workgroup of
+    // the next launch appends their totals.  An odd step goes first, so a run
+    // ends with a two-step launch or is a single step.
+    const bool pairs = !mom && run_pairs(h, tb);
+    const int nc = total_parts_of(h);
+    TotalsArgs prev[2];
+    int nprev = 0, cur = from;
+    for (int k = 0, launch = 0; k < count; ++launch) {
+        double *buf = tb.partials + (size_t)(launch & 1) * nc * tb.parts;
+        const int steps = pairs && (count - k) % 2 == 0 ? 2 : 1;
+        const bool last = k + steps == count;
+        const void *src = path ? (k == 0 ? path->start : path->tmp[(launch - 1) & 1]) : h->buf[cur];
+        void *dst = path ? (last ? path->end : path->tmp[launch & 1]) : h->buf[cur ^ 1];
+        if (steps == 2) {
+            MarchArgs a = march_args(h);
+            const size_t parts = (size_t)march_parts(h);
+            a.src = src;
+            a.dst = dst;
+            a.partials[0] = buf;
+            a.partials[1] = buf + parts * nc;
+            if (last) {
+                a.rho_out = rho;
+                a.u_out = u;
+            }
+            a.nprev = nprev;
+            std::copy(prev, prev + 2, a.prev);
+            HIP_OR_FAIL(launch_march2(a, s));
+            prev[0] = totals_args(h, a.partials[0], (int)parts, tb, cur);
+            prev[1] = totals_args(h, a.partials[1], (int)parts, tb, cur ^ 1);
+        } else {
+            const bool fields = rho && last;
+            StepArgs a = step_args(h, cur, mom ? mom[k] : (fields ? rho : nullptr), fields ? u : nullptr);
+            a.mom_rec = mom ? 1 : 0;
+            a.src = src;
+            a.dst = dst;
+            a.partials = buf;
+            a.nprev = nprev;
+            std::copy(prev, prev + 2, a.prev);
+            if (h->inplace)
+                HIP_OR_FAIL(launch_aa_step(h->codec, h->variant, h->solids, cur == 0, a, h->grid, s));
+            else
+                HIP_OR_FAIL(launch_step(h->codec, h->variant, h->solids, mom != nullptr || fields, a, h->grid, s));
+            prev[0] = totals_args(h, buf, h->grid, tb, cur);
         }
-        a.partials = tb.partials + (size_t)(k & 1) * 4 * h->grid;
-        if (k > 0) a.prev = totals_args(h, (k - 1) & 1, tb, from ^ ((k - 1) & 1));
-        HIP_OR_FAIL(launch_step(h->codec, h->variant, h->solids, mom != nullptr, a, h->grid, s));
+        nprev = totals ? steps : 0;
+        cur ^= 1;
+        k += steps;
     }
-    HIP_OR_FAIL(launch_totals(totals_args(h, (count - 1) & 1, tb, from ^ ((count - 1) & 1)), s));
+    if (nprev > 0) HIP_OR_FAIL(launch_totals(prev, nprev, s));
     return LB_OK;
+}
+
+// The array a run of count steps from buf[from] ends in.
+int run_end(const lb_lattice *h, int from, int count, const TotalsBufs &tb)
+{
+    return from ^ ((run_pairs(h, tb) ? count / 2 + count % 2 : count) & 1);
 }
 
 // Capture the run of len steps from buf[parity] unless it is held already
@@ -438,34 +551,55 @@ int prepare_graphs(lb_lattice *h, int n)
     if (n < kGraphMin) return LB_OK;
     const int len = std::min(n, kGraphMax);
     if (int rc = ensure_graph(h, len, h->cur)) return rc;
-    if ((len & 1) && n >= 2 * len) return ensure_graph(h, len, h->cur ^ 1);
+    const int end = run_end(h, h->cur, len, own_bufs(h));
+    if (end != h->cur && n >= 2 * len) return ensure_graph(h, len, end);
     return LB_OK;
 }
 
 int enqueue_steps(lb_lattice *h, int n, float *rho, float *u)
 {
-    int plain = rho ? n - 1 : n;
+    const TotalsBufs tb = own_bufs(h);
+    // the row kernels write the last step's fields in its own launch, the
+    // last of a run; the others in a launch of one step
+    const bool row_fields = rho && !h->inplace && h->variant != 0;
+    const int fields_steps = !rho ? 0 : (row_fields ? (run_pairs(h, tb) && n >= 2 ? 2 : 1) : 1);
+    int plain = n - fields_steps;
     if (plain >= kGraphMin) {
         const int len = std::min(plain, kGraphMax);
         while (plain >= len) {
             if (int rc = run_graph(h, len, h->cur)) return rc;
-            h->cur ^= len & 1;
+            h->cur = run_end(h, h->cur, len, tb);
             h->steps += len;
             plain -= len;
         }
     }
-    if (plain > 0) {
-        int rc = enqueue_run(h, h->cur, plain, h->stream, own_bufs(h));
+    const int run = plain + (row_fields ? fields_steps : 0);
+    if (run > 0) {
+        int rc = enqueue_run(h, h->cur, run, h->stream, tb, nullptr, nullptr, row_fields ? rho : nullptr, u);
         if (rc) return rc;
-        h->cur ^= plain & 1;
-        h->steps += plain;
+        h->cur = run_end(h, h->cur, run, tb);
+        h->steps += run;
     }
-    if (rho) {
-        int rc = enqueue_one(h, h->cur, rho, u, h->stream, own_bufs(h));
+    if (rho && !row_fields) {
+        int rc = enqueue_one(h, h->cur, rho, u, h->stream, tb);
         if (rc) return rc;
         h->cur ^= 1;
         h->steps += 1;
     }
+    return LB_OK;
+}
+
+// The buffers of the per-step totals for runs of parts partials per launch:
+// two buffers of them, and one slot per reduce workgroup for two steps.
+int alloc_partials(lb_lattice *h, size_t parts)
+{
+    if (h->partials) (void)hipFree(h->partials);
+    if (h->gpartials) (void)hipFree(h->gpartials);
+    h->partials = h->gpartials = nullptr;
+    const size_t nc = max_total_parts(h), ngroups = (parts + kRedChunk - 1) / kRedChunk;
+    if (hipMalloc(&h->partials, parts * 2 * nc * sizeof(double)) != hipSuccess ||
+        hipMalloc(&h->gpartials, ngroups * 2 * nc * sizeof(double)) != hipSuccess)
+        return fail(LB_ENOMEM, "hipMalloc(partials)");
     return LB_OK;
 }
 
@@ -615,6 +749,21 @@ int create_impl(lb_lattice **out, int nx, int ny, int nz, double tau, const uint
     // the tile count fits the grid.
     const uint64_t tiles = (n / h->vsites + kBlock - 1) / kBlock;
     h->grid = (int)(tiles < 1 ? 1 : tiles);
+    // Two steps per launch for FP32 lattices in two arrays, where the launch
+    // shape says it pays (LB_TWO_STEP=0: never, 2: always).  Not with solids
+    // (the masks' address selections and the second step's choice between own
+    // and neighbours' values cost more than the saved traffic: 256x128x128
+    // channel 102 us a step in one-step launches, 113 in pairs; 128^3 sphere
+    // 63 and 59) nor, as long as one is set, with a force field (128^3: 57 and
+    // 63, with solids 64 and 83).
+    // Their totals are split into parts whose sums do not depend on how a run
+    // is cut into launches, and so are those of the same lattice in one array.
+    const long two = env_long("LB_TWO_STEP", 1);
+    if (storage == LB_F32 && !h->solids && h->variant != 0) {
+        h->march = march_shape(nx, ny, nz, h->cus);
+        if (h->march.use || two != 1) h->split = total_split(n);
+        h->march.use = !inplace && (two == 2 || (two == 1 && h->march.use));
+    }
 
     auto bail = [&](int code, const char *what, hipError_t e) {
         release(h);
@@ -641,18 +790,14 @@ int create_impl(lb_lattice **out, int nx, int ny, int nz, double tau, const uint
         if (e != hipSuccess) return bail(LB_EHIP, "hipMemsetAsync", e);
     }
     if (h->inplace) h->buf[1] = h->buf[0];  // steps read and write the one array
-    // per-step totals: one slot per step workgroup (two buffers, for runs of
-    // steps) and one per reduce workgroup
-    const size_t ngroups = ((size_t)h->grid + kRedChunk - 1) / kRedChunk;
-    if ((e = hipMalloc(&h->partials, (size_t)h->grid * 8 * sizeof(double))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
-    if ((e = hipMalloc(&h->gpartials, ngroups * 4 * sizeof(double))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
-    if ((e = hipMalloc(&h->ticket, sizeof(unsigned int))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
+    if (alloc_partials(h, buf_parts(h)) != LB_OK) return bail(LB_ENOMEM, "hipMalloc(partials)", hipErrorOutOfMemory);
+    if ((e = hipMalloc(&h->ticket, kTickets * sizeof(unsigned int))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
     if ((e = hipMalloc(&h->ring, (size_t)kRingCap * 4 * sizeof(double))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
     if ((e = hipMalloc(&h->counter, sizeof(unsigned long long))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
     // J, then the per-workgroup parts of its sum
     if ((e = hipMalloc(&h->jval, (1 + (size_t)outlet_parts(ny, nz)) * sizeof(double))) != hipSuccess)
         return bail(LB_ENOMEM, "hipMalloc", e);
-    if ((e = hipMemsetAsync(h->ticket, 0, sizeof(unsigned int), h->stream)) != hipSuccess) return bail(LB_EHIP, "hipMemsetAsync", e);
+    if ((e = hipMemsetAsync(h->ticket, 0, kTickets * sizeof(unsigned int), h->stream)) != hipSuccess) return bail(LB_EHIP, "hipMemsetAsync", e);
     if ((e = hipMemsetAsync(h->counter, 0, sizeof(unsigned long long), h->stream)) != hipSuccess) return bail(LB_EHIP, "hipMemsetAsync", e);
     if ((e = hipMemsetAsync(h->ring, 0, (size_t)kRingCap * 4 * sizeof(double), h->stream)) != hipSuccess) return bail(LB_EHIP, "hipMemsetAsync", e);
     if (storage == LB_S16) {
@@ -775,20 +920,23 @@ int lb_step_noalloc(lb_lattice *h, int n)
 {
     if (int rc = check(h)) return rc;
     if (n < 0) return fail(LB_EINVAL, "step count must be >= 0 (got %d)", n);
-    const size_t need = scratch_need(h);
-    if (need > kScratchBytes)
+    // two steps per launch where their partials fit as well
+    size_t parts = buf_parts(h);
+    if (scratch_need(h, parts) > scratch_limit(h)) parts = (size_t)h->grid;
+    const size_t need = scratch_need(h, parts);
+    if (need > scratch_limit(h))
         return fail(LB_EINVAL,
                     "lb_step_noalloc: the totals of this lattice need %zu bytes of scratch (%d step workgroups); "
                     "the library's static scratch holds %zu bytes",
-                    need, h->grid, kScratchBytes);
+                    need, h->grid, scratch_limit(h));
     if (n == 0) return LB_OK;
     unsigned char *base = scratch_base(h->dev);
     if (!base) return fail(LB_ESTATE, "scratch address of device %d not resolved", h->dev);
-    const TotalsBufs tb = scratch_bufs(h, base);
-    // the ticket must start at zero: a kernel, not a memset, clears it
-    HIP_OR_FAIL(launch_zero_words(tb.ticket, 1, h->stream));
+    const TotalsBufs tb = scratch_bufs(h, base, parts);
+    // the tickets must start at zero: a kernel, not a memset, clears them
+    HIP_OR_FAIL(launch_zero_words(tb.ticket, kTickets, h->stream));
     if (int rc = enqueue_run(h, h->cur, n, h->stream, tb)) return rc;
-    h->cur ^= n & 1;
+    h->cur = run_end(h, h->cur, n, tb);
     h->steps += n;
     return LB_OK;
 }
@@ -844,13 +992,7 @@ int lb_set_force_field(lb_lattice *h, const float *fx)
         const uint64_t tiles = (h->n / h->vsites + kBlock - 1) / kBlock;
         h->grid = (int)std::min<uint64_t>(tiles, 0x7fffffffull);
         HIP_OR_FAIL(hipStreamSynchronize(h->stream));
-        (void)hipFree(h->partials);
-        (void)hipFree(h->gpartials);
-        h->partials = h->gpartials = nullptr;
-        const size_t ngroups = ((size_t)h->grid + kRedChunk - 1) / kRedChunk;
-        if (hipMalloc(&h->partials, (size_t)h->grid * 8 * sizeof(double)) != hipSuccess ||
-            hipMalloc(&h->gpartials, ngroups * 4 * sizeof(double)) != hipSuccess)
-            return fail(LB_ENOMEM, "hipMalloc(partials)");
+        if (int rc = alloc_partials(h, buf_parts(h))) return rc;
     }
     h->graphs.invalidate();
     return LB_OK;
@@ -953,11 +1095,8 @@ int grad_impl(lb_lattice *h, int nsteps, int every, const float *seed, float *gr
     for (int k = 0; k < nck && rc == LB_OK; ++k) {
         const int len = std::min(every, nsteps - k * every);
         const bool last = k == nck - 1;
-        std::vector<void *> path(len + 1);
-        path[0] = ck[k];
-        for (int j = 1; j < len; ++j) path[j] = tmp[j & 1];
-        path[len] = last ? h->buf[final_cur] : ck[k + 1];
-        rc = enqueue_run(h, h->cur, len, h->stream, own_bufs(h), path.data(), last ? mom.data() : nullptr);
+        const RunPath path{ck[k], last ? h->buf[final_cur] : ck[k + 1], {tmp[0], tmp[1]}};
+        rc = enqueue_run(h, h->cur, len, h->stream, own_bufs(h), &path, last ? mom.data() : nullptr);
     }
     if (rc == LB_OK) {
         h->cur = final_cur;
@@ -986,13 +1125,10 @@ int grad_impl(lb_lattice *h, int nsteps, int every, const float *seed, float *gr
     bool first = true;
     for (int k = nck - 1; k >= 0 && rc == LB_OK; --k) {
         const int start = k * every, stop = std::min(start + every, nsteps);
-        for (int j = 0; j < stop - start && rc == LB_OK && k < nck - 1; ++j) {
-            StepArgs a = step_args(h, 0, mom[j], nullptr);
-            a.mom_rec = 1;
-            a.src = j == 0 ? ck[k] : tmp[(j - 1) & 1];
+        if (k < nck - 1) {
             // the stretch's last state is not needed: that step writes its moments only
-            a.dst = j + 1 < stop - start ? tmp[j & 1] : nullptr;
-            hip(launch_step(h->codec, h->variant, h->solids, true, a, h->grid, h->stream), "recompute step");
+            const RunPath path{ck[k], nullptr, {tmp[0], tmp[1]}};
+            rc = enqueue_run(h, 0, stop - start, h->stream, own_bufs(h), &path, mom.data(), nullptr, nullptr, false);
         }
         for (int n = stop - 1; n >= start && rc == LB_OK; --n) {
             AdjArgs a{};
@@ -1199,6 +1335,7 @@ long long lb_query(const lb_lattice *h, int key)
         case 10: return h->rescales;
         case 11: return h->tile_order;
         case 12: return h->pull_nt;
+        case 13: return h->march.use ? 2 : 1;
         default: return -1;
     }
 }
@@ -1253,13 +1390,7 @@ int lb_tune(lb_lattice *h, int reps)
     // partials for the largest grid (timing launches, and the choice)
     if (max_grid > h->grid) {
         HIP_OR_FAIL(hipStreamSynchronize(h->stream));
-        (void)hipFree(h->partials);
-        (void)hipFree(h->gpartials);
-        h->partials = h->gpartials = nullptr;
-        const size_t ngroups = ((size_t)max_grid + kRedChunk - 1) / kRedChunk;
-        if (hipMalloc(&h->partials, (size_t)max_grid * 8 * sizeof(double)) != hipSuccess ||
-            hipMalloc(&h->gpartials, ngroups * 4 * sizeof(double)) != hipSuccess)
-            return fail(LB_ENOMEM, "hipMalloc(partials)");
+        if (int rc = alloc_partials(h, std::max((size_t)max_grid, buf_parts(h)))) return rc;
     }
     // every timing launch reads the current state and writes the other array,
     // and, like a step inside a run, its first workgroup appends the totals
@@ -1288,16 +1419,19 @@ int lb_tune(lb_lattice *h, int reps)
         if (hipMemsetAsync(tctr, 0, sizeof(unsigned long long), h->stream) != hipSuccess) rc = fail(LB_EHIP, "memset");
         auto launch = [&](int k) {
             StepArgs a = step_args(h, h->cur, nullptr, nullptr, c.variant);
-            a.partials = h->partials + (size_t)(k & 1) * 4 * c.grid;
+            const size_t nc = total_parts_of(h);
+            a.partials = h->partials + (size_t)(k & 1) * nc * c.grid;
             if (k > 0) {
                 TotalsArgs t{};
-                t.partials = h->partials + (size_t)((k - 1) & 1) * 4 * c.grid;
+                t.nc = (int)nc;
+                t.partials = h->partials + (size_t)((k - 1) & 1) * nc * c.grid;
                 t.nparts = c.grid;
                 t.gpartials = h->gpartials;
                 t.ring = tring;
                 t.step_counter = tctr;
                 t.n_fluid = h->n_fluid;
-                a.prev = t;
+                a.nprev = 1;
+                a.prev[0] = t;
             }
             if (launch_step(h->codec, c.variant, h->solids, false, a, c.grid, h->stream) != hipSuccess)
                 rc = fail(LB_EHIP, "step kernel launch");
@@ -1343,12 +1477,13 @@ int lb_time_step_kernel(lb_lattice *h, int n, double *ms)
         if (rc == LB_OK && hipEventCreate(&e) != hipSuccess) rc = fail(LB_EHIP, "hipEventCreate");
     for (int k = 0; k < n && rc == LB_OK; ++k) {
         StepArgs a = step_args(h, h->cur, nullptr, nullptr);
+        const TotalsArgs t = totals_args(h, h->partials, h->grid, own_bufs(h), h->cur);
         if (hipEventRecord(ev[2 * k], h->stream) != hipSuccess) rc = fail(LB_EHIP, "hipEventRecord");
         const hipError_t le = h->inplace ? launch_aa_step(h->codec, h->variant, h->solids, h->cur == 0, a, h->grid, h->stream)
                                          : launch_step(h->codec, h->variant, h->solids, false, a, h->grid, h->stream);
         if (rc == LB_OK && le != hipSuccess) rc = fail(LB_EHIP, "step kernel launch");
         if (rc == LB_OK && hipEventRecord(ev[2 * k + 1], h->stream) != hipSuccess) rc = fail(LB_EHIP, "hipEventRecord");
-        if (rc == LB_OK && launch_totals(totals_args(h, 0, own_bufs(h), h->cur), h->stream) != hipSuccess) rc = fail(LB_EHIP, "totals launch");
+        if (rc == LB_OK && launch_totals(&t, 1, h->stream) != hipSuccess) rc = fail(LB_EHIP, "totals launch");
         if (rc == LB_OK) {
             h->cur ^= 1;
             h->steps += 1;

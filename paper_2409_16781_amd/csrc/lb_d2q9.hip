@@ -93,6 +93,7 @@ Step2Args step2_args(const lb2d_lattice *h, int from)
 TotalsArgs totals2(const lb2d_lattice *h, int buf)
 {
     TotalsArgs t{};
+    t.nc = 4;
     t.partials = h->partials + (size_t)buf * 4 * h->grid;
     t.nparts = h->grid;
     t.gpartials = h->gpartials;
@@ -117,7 +118,10 @@ int enqueue2(lb2d_lattice *h, int n)
         h->cur ^= 1;
         h->steps += 1;
     }
-    if (n > 0) HIP_OR_FAIL(launch_totals(totals2(h, (n - 1) & 1), h->stream));
+    if (n > 0) {
+        const TotalsArgs t = totals2(h, (n - 1) & 1);
+        HIP_OR_FAIL(launch_totals(&t, 1, h->stream));
+    }
     return LB_OK;
 }
 
@@ -211,9 +215,9 @@ lb2d_lattice *lb2d_create(int nx, int ny, double tau, const uint8_t *flags, doub
     if ((e = hipMalloc(&h->partials, (size_t)h->grid * 8 * sizeof(double))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
     if ((e = hipMalloc(&h->gpartials, ngroups * 4 * sizeof(double))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
     if ((e = hipMalloc(&h->ring, (size_t)kRingCap * 4 * sizeof(double))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
-    if ((e = hipMalloc(&h->ticket, sizeof(unsigned int))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
+    if ((e = hipMalloc(&h->ticket, kTickets * sizeof(unsigned int))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
     if ((e = hipMalloc(&h->counter, sizeof(unsigned long long))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
-    if ((e = hipMemsetAsync(h->ticket, 0, sizeof(unsigned int), h->stream)) != hipSuccess) return bail(LB_EHIP, "hipMemsetAsync", e);
+    if ((e = hipMemsetAsync(h->ticket, 0, kTickets * sizeof(unsigned int), h->stream)) != hipSuccess) return bail(LB_EHIP, "hipMemsetAsync", e);
     if ((e = hipMemsetAsync(h->counter, 0, sizeof(unsigned long long), h->stream)) != hipSuccess) return bail(LB_EHIP, "hipMemsetAsync", e);
     if ((e = hipMemsetAsync(h->ring, 0, (size_t)kRingCap * 4 * sizeof(double), h->stream)) != hipSuccess) return bail(LB_EHIP, "hipMemsetAsync", e);
     if (h->solids) {

@@ -198,8 +198,8 @@ __global__ __launch_bounds__(kBlock) void step2d(Step2Args a)
             acc[2] += (t[3] - t[4]) + (t[5] - t[6]) + (t[7] - t[8]);
         }
     }
-    store_block_totals(acc, a.partials + 4 * (size_t)blockIdx.x);
-    if (a.prev.partials != nullptr && blockIdx.x == 0) append_step_totals(a.prev);
+    store_block_totals<4>(acc, a.partials + 4 * (size_t)blockIdx.x);
+    if (a.prev.partials != nullptr && blockIdx.x == 0) append_step_totals<4>(a.prev);
 }
 
 // bit i (1..8): site x - c_i is solid; bit 8 + i: it is the lid; bit 31: the site is solid.

@@ -451,18 +451,50 @@ __device__ __forceinline__ void st_elem(char *base, uint64_t idx, uint32_t b)
 __device__ __forceinline__ void relax_pair(float &gi, float &gj, float s, float n, float cj, float inv, float base,
                                            float q, float hC, float hD, float hom, float &sum_hs)
 {
+#pragma clang fp contract(off)
     const float cu = cj * inv;
-    const float hs = cu * (q * cj + hC) + base - hom * s;
-    const float hd = hD - hom * n;
+    const float hs = __builtin_fmaf(-hom, s, __builtin_fmaf(cu, __builtin_fmaf(q, cj, hC), base));
+    const float hd = __builtin_fmaf(-hom, n, hD);
+    gi = gi + (hs + hd);
+    gj = gj + (hs - hd);
+    sum_hs += hs;
+}
+
+// The same with the force terms formed from c.F of a site's own force:
+// hC = 3 g3 c.F, hD = g3 c.F with g3 = 3 (1 - omega/2) w_k.
+__device__ __forceinline__ void relax_pair_field(float &gi, float &gj, float s, float n, float cj, float inv, float base,
+                                                 float q, float g3, float cF, float hom, float &sum_hs)
+{
+#pragma clang fp contract(off)
+    const float cu = cj * inv;
+    const float hs =
+        __builtin_fmaf(-hom, s, __builtin_fmaf(cu, __builtin_fmaf(3.0f * g3, cF, q * cj), base));
+    const float hd = __builtin_fmaf(g3, cF, -(hom * n));
     gi = gi + (hs + hd);
     gj = gj + (hs - hd);
     sum_hs += hs;
 }
 
 // In: g[19] gathered pre-collision values.  Out: g[19] post-collision values,
-// rho and u (pre-collision moments, u with the half-force shift).
-__device__ __forceinline__ void collide(float (&g)[kQ], const Coll &p, float &rho, float &ux, float &uy, float &uz)
+// rho and u (pre-collision moments, u with the half-force shift).  kForce =
+// false: the force is zero.  The terms it enters are then literal zeros or
+// left out, which changes no bits but the sign of a zero: the same additions
+// and fused multiply-adds round the same values.  (With a force the kernel
+// spends 25 of its 190 instructions a site on these terms, 18 of them moves
+// of the per-direction constants from scalar registers.)
+// kField 1, 2: the x-force of this site is fx (the uniform one plus the
+// field's).  2 sums j.u and u.F from x on, 1 (and 0) from y on, the order that
+// each force-field kernel has had (an outlet flux is compared to 1e-9, and
+// another order moves it by 1e-8).
+template <bool kForce = true, int kField = 0>
+__device__ __forceinline__ void collide(float (&g)[kQ], const Coll &p, float &rho, float &ux, float &uy, float &uz,
+                                        float fx = 0.0f)
 {
+    // every fused multiply-add is written out: a kernel that contracted a sum
+    // of products its own way would round differently from the others
+#pragma clang fp contract(off)
+    static_assert(kForce || kField == 0, "a force field is a force");
+    const float Fx = kField ? fx : p.fx, hFx = kField ? 0.5f * fx : p.hfx;
     const float s1 = g[1] + g[2], d1 = g[1] - g[2];
     const float s3 = g[3] + g[4], d3 = g[3] - g[4];
     const float s5 = g[5] + g[6], d5 = g[5] - g[6];
@@ -473,9 +505,9 @@ __device__ __forceinline__ void collide(float (&g)[kQ], const Coll &p, float &rh
     const float s15 = g[15] + g[18], d15 = g[15] - g[18];
     const float s16 = g[16] + g[17], d16 = g[16] - g[17];
     const float drho = g[0] + ((s1 + s3) + (s5 + s7)) + ((s8 + s11) + (s12 + s15)) + s16;
-    const float jx = (d1 + d7 + d8 + d11 + d12) + p.hfx;
-    const float jy = (d3 + d7 - d8 + d15 + d16) + p.hfy;
-    const float jz = (d5 + d11 - d12 + d15 - d16) + p.hfz;
+    const float jx = kForce ? (d1 + d7 + d8 + d11 + d12) + hFx : d1 + d7 + d8 + d11 + d12;
+    const float jy = kForce ? (d3 + d7 - d8 + d15 + d16) + p.hfy : d3 + d7 - d8 + d15 + d16;
+    const float jz = kForce ? (d5 + d11 - d12 + d15 - d16) + p.hfz : d5 + d11 - d12 + d15 - d16;
     rho = 1.0f + drho;
     // 1/rho enters only the second-order terms and the reported velocity; the
     // hardware reciprocal (1 ulp) is accurate enough for both
@@ -483,32 +515,53 @@ __device__ __forceinline__ void collide(float (&g)[kQ], const Coll &p, float &rh
     ux = jx * inv;
     uy = jy * inv;
     uz = jz * inv;
-    const float ju = jx * ux + jy * uy + jz * uz;  // rho u.u
-    const float uF = ux * p.fx + uy * p.fy + uz * p.fz;
-    const float t = drho - 1.5f * ju;
-    const float base1 = p.ow1 * t - p.g31 * uF, base2 = p.ow2 * t - p.g32 * uF;
+    const float ju = kField == 2 ? __builtin_fmaf(jz, uz, __builtin_fmaf(jy, uy, jx * ux))
+                                 : __builtin_fmaf(jz, uz, __builtin_fmaf(jx, ux, jy * uy));  // rho u.u
+    const float t = __builtin_fmaf(-1.5f, ju, drho);
+    float base1, base2;
+    if constexpr (kForce) {
+        const float uF = kField == 2 ? __builtin_fmaf(uz, p.fz, __builtin_fmaf(uy, p.fy, ux * Fx))
+                                     : __builtin_fmaf(uz, p.fz, __builtin_fmaf(ux, Fx, uy * p.fy));
+        base1 = __builtin_fmaf(p.ow1, t, -(p.g31 * uF));
+        base2 = __builtin_fmaf(p.ow2, t, -(p.g32 * uF));
+    } else {
+        base1 = p.ow1 * t;
+        base2 = p.ow2 * t;
+    }
 
     // odd non-equilibrium parts: diagonals directly, axes as the remainder
     const float c7 = jx + jy, c8 = jx - jy, c11 = jx + jz, c12 = jx - jz, c15 = jy + jz, c16 = jy - jz;
     constexpr float kSixth = 1.0f / 6.0f;
-    const float n7 = d7 - kSixth * c7, n8 = d8 - kSixth * c8;
-    const float n11 = d11 - kSixth * c11, n12 = d12 - kSixth * c12;
-    const float n15 = d15 - kSixth * c15, n16 = d16 - kSixth * c16;
-    const float n1 = -p.hfx - ((n7 + n8) + (n11 + n12));
-    const float n3 = -p.hfy - ((n7 - n8) + (n15 + n16));
-    const float n5 = -p.hfz - ((n11 - n12) + (n15 - n16));
+    const float n7 = __builtin_fmaf(-kSixth, c7, d7), n8 = __builtin_fmaf(-kSixth, c8, d8);
+    const float n11 = __builtin_fmaf(-kSixth, c11, d11), n12 = __builtin_fmaf(-kSixth, c12, d12);
+    const float n15 = __builtin_fmaf(-kSixth, c15, d15), n16 = __builtin_fmaf(-kSixth, c16, d16);
+    const float n1 = kForce ? -hFx - ((n7 + n8) + (n11 + n12)) : -((n7 + n8) + (n11 + n12));
+    const float n3 = kForce ? -p.hfy - ((n7 - n8) + (n15 + n16)) : -((n7 - n8) + (n15 + n16));
+    const float n5 = kForce ? -p.hfz - ((n11 - n12) + (n15 - n16)) : -((n11 - n12) + (n15 - n16));
 
     float sum_hs = 0.0f;
-    relax_pair(g[1], g[2], s1, n1, jx, inv, base1, p.q1, p.hC[1], p.hD[1], p.hom, sum_hs);
-    relax_pair(g[3], g[4], s3, n3, jy, inv, base1, p.q1, p.hC[3], p.hD[3], p.hom, sum_hs);
-    relax_pair(g[5], g[6], s5, n5, jz, inv, base1, p.q1, p.hC[5], p.hD[5], p.hom, sum_hs);
-    relax_pair(g[7], g[10], s7, n7, c7, inv, base2, p.q2, p.hC[7], p.hD[7], p.hom, sum_hs);
-    relax_pair(g[8], g[9], s8, n8, c8, inv, base2, p.q2, p.hC[8], p.hD[8], p.hom, sum_hs);
-    relax_pair(g[11], g[14], s11, n11, c11, inv, base2, p.q2, p.hC[11], p.hD[11], p.hom, sum_hs);
-    relax_pair(g[12], g[13], s12, n12, c12, inv, base2, p.q2, p.hC[12], p.hD[12], p.hom, sum_hs);
-    relax_pair(g[15], g[18], s15, n15, c15, inv, base2, p.q2, p.hC[15], p.hD[15], p.hom, sum_hs);
-    relax_pair(g[16], g[17], s16, n16, c16, inv, base2, p.q2, p.hC[16], p.hD[16], p.hom, sum_hs);
-    g[0] = g[0] - 2.0f * sum_hs;
+    auto pair = [&](int i, int j, float s, float n, float cj) __attribute__((always_inline)) {
+        const bool axis = weight_class(i) == 1;
+        const float base = axis ? base1 : base2, q = axis ? p.q1 : p.q2;
+        if constexpr (kField) {
+            const float a = CX[i] ? Fx : p.fy;  // the first of c's one or two components is +1
+            const float b = CZ[i] ? (float)CZ[i] * p.fz : (float)CY[i] * p.fy;
+            const float cF = i < 7 ? (CZ[i] ? p.fz : a) : a + b;
+            relax_pair_field(g[i], g[j], s, n, cj, inv, base, q, axis ? p.g31 : p.g32, cF, p.hom, sum_hs);
+        } else {
+            relax_pair(g[i], g[j], s, n, cj, inv, base, q, kForce ? p.hC[i] : 0.0f, kForce ? p.hD[i] : 0.0f, p.hom, sum_hs);
+        }
+    };
+    pair(1, 2, s1, n1, jx);
+    pair(3, 4, s3, n3, jy);
+    pair(5, 6, s5, n5, jz);
+    pair(7, 10, s7, n7, c7);
+    pair(8, 9, s8, n8, c8);
+    pair(11, 14, s11, n11, c11);
+    pair(12, 13, s12, n12, c12);
+    pair(15, 18, s15, n15, c15);
+    pair(16, 17, s16, n16, c16);
+    g[0] = __builtin_fmaf(-2.0f, sum_hs, g[0]);
 }
 
 // Per-direction totals -> {mass deviation, momentum} of a group of sites
@@ -553,17 +606,64 @@ __device__ __forceinline__ void moments_of_totals_by_class(const int (&t)[kQ], i
     pz[2] = (d11 - d12) + (d15 - d16);
 }
 
+// Totals of a launch are sums of per-site moments over all its workgroups.
+// With FP16 and scaled 16-bit storage every stored value is a multiple of one
+// quantum, the FP64 sums are exact, and any grouping of the sites gives the
+// same bits.  FP32 values have no common quantum: there each site's moment m
+// is split into two multiples of fixed quanta,
+//   hi = (m + M1) - M1,   lo = ((m - hi) + M2) - M2,
+// chosen for the lattice's size (total_split) so that sums of hi and sums of
+// lo are both exact.  hi + lo differs from m by at most half of the second
+// quantum (2^-52 at 512^3, less on smaller lattices), the same for a site
+// whichever kernel computes it, so the totals of a step do not depend on how
+// the sites were dealt to lanes, workgroups or launches: a step taken as half
+// of a two-step launch gives the bits of one taken alone.  (24 more additions
+// a site: 0 to 2% of an FP32 step, 3% where it works from the caches.)
+// Only lattices that take two-step launches (and in-place ones of the same
+// extents) split: NC = 8 doubles of totals instead of 4, a template argument
+// of the vector-row steps.
+template <int NC>
+__device__ __forceinline__ void add_moments(double m, double px, double py, double pz, double (&acc)[NC],
+                                            const TotalSplit &sp)
+{
+    const double v[4] = {m, px, py, pz};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if constexpr (NC == 8) {
+            const double hi = (v[k] + sp.m1) - sp.m1;
+            const double lo = ((v[k] - hi) + sp.m2) - sp.m2;
+            acc[k] += hi;
+            acc[4 + k] += lo;
+        } else {
+            acc[k] += v[k];
+        }
+    }
+}
+
 // FP64 totals of the values a lane stores: every stored element is converted
-// to double and summed per direction, then the directions are combined into
-// {mass deviation, momentum}, all in FP64 and in a fixed order (dead
-// elements hold zero and add nothing).  The stored values are exact in
-// double, so a lane's totals carry only FP64 rounding (~1e-16 relative).
-template <int C, int NW>
-__device__ __forceinline__ void add_lane_totals(const Lane<NW> (&d)[kQ], double (&acc)[4], const Scale16 &sc)
+// to double and combined into {mass deviation, momentum} in FP64 and in a
+// fixed order (dead elements hold zero and add nothing).  The stored values
+// are exact in double, so a lane's totals carry only FP64 rounding (~1e-16
+// relative).  NC = 4: a lane's sites are summed per direction first (fewer
+// additions); NC = 8: each site's moments are split and summed by parts.
+template <int C, int NW, int NC>
+__device__ __forceinline__ void add_lane_totals(const Lane<NW> (&d)[kQ], double (&acc)[NC], const Scale16 &sc,
+                                                const TotalSplit &sp)
 {
     using K = Codec<C>;
     constexpr int V = NW * 4 / K::kBytes;
     double m, px, py, pz;
+    if constexpr (NC == 8) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            double t[kQ];
+#pragma unroll
+            for (int i = 0; i < kQ; ++i) t[i] = (double)K::dec(vget<C, NW>(d[i], e));
+            moments_of_totals(t, m, px, py, pz);
+            add_moments<NC>(m, px, py, pz, acc, sp);
+        }
+        return;
+    }
     if constexpr (C == kS16) {
         // The codes are integers: the lane's mass and momentum per weight
         // class are exact int32 sums (|sum| < 12 V 2^15), each scaled once by
@@ -593,98 +693,135 @@ __device__ __forceinline__ void add_lane_totals(const Lane<NW> (&d)[kQ], double 
         }
         moments_of_totals(t, m, px, py, pz);
     }
-    acc[0] += m;
-    acc[1] += px;
-    acc[2] += py;
-    acc[3] += pz;
+    add_moments<NC>(m, px, py, pz, acc, sp);
 }
 
 // ------------------------------------------------- FP64 totals per launch --
 // Each workgroup of a step reduces its threads' FP64 totals (through LDS in a
-// fixed tree) and stores them in its slot of the partials; no fence
-// or atomic is needed there, because the totals are reduced by a second,
-// stream-ordered kernel (reduce_totals).  Every addition happens in a fixed
-// order, so the totals are bitwise reproducible.
+// fixed tree) and stores them in its slot of the partials (NC doubles); no
+// fence or atomic is needed there, because the totals are reduced by a later,
+// stream-ordered kernel (the next step of a run, or reduce_totals).  Every
+// addition happens in a fixed order, so the totals are bitwise reproducible.
 
-__device__ __forceinline__ void store_block_totals(const double (&acc)[4], double *out)
+// The NC sums over a wave of the lanes' v, one component per lane: at each of
+// the first log2 NC levels of the butterfly a lane passes on half of its
+// components and keeps the other half, so the six levels take NC + 5 - log2 NC
+// exchanges instead of 6 NC (for NC = 8: 10 instead of 48, the additions of
+// each component being those of the full butterfly).  Returns the sum of
+// component wave_component<NC>(lane).
+template <int NC>
+__device__ __forceinline__ double wave_reduce(double (&v)[NC])
 {
-    // a butterfly within each wave, then the four wave sums through 128 bytes
-    // of LDS (a small footprint keeps more workgroups resident per CU)
-    __shared__ double red[kBlock / 64][4];
-    double v[4];
+    const int lane = threadIdx.x & 63;
+    int off = 32;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        v[k] = acc[k];
+    for (int n = NC / 2; n >= 1; n /= 2, off /= 2) {
+        const bool up = (lane & off) != 0;
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
+        for (int k = 0; k < n; ++k) {
+            const double send = up ? v[k] : v[k + n];
+            v[k] = (up ? v[k + n] : v[k]) + __shfl_xor(send, off, 64);
+        }
     }
-    if ((threadIdx.x & 63) == 0) {
+    double x = v[0];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) red[threadIdx.x >> 6][k] = v[k];
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) out[k] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
-    }
+    for (; off >= 1; off /= 2) x += __shfl_xor(x, off, 64);
+    return x;
 }
 
-// Sum v[0..count) (4 doubles each) in a fixed tree; the result is valid in thread 0.
-__device__ __forceinline__ void block_sum4(const double *v, int count, double (&out)[4], bool coherent)
+// Component held by a lane after wave_reduce (the lowest 64 / NC lanes of
+// each group hold the same).
+template <int NC>
+__device__ __forceinline__ int wave_component(int lane)
 {
-    __shared__ double tot[4][kBlock];
-    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    return lane / (64 / NC);
+}
+
+template <int NC>
+__device__ __forceinline__ void store_block_totals(const double (&acc)[NC], double *out)
+{
+    // one component per lane of each wave, then the four wave sums through a
+    // few hundred bytes of LDS (a small footprint keeps more workgroups
+    // resident per CU)
+    __shared__ double red[kBlock / 64][NC];
+    double v[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) v[k] = acc[k];
+    const double x = wave_reduce<NC>(v);
+    const int lane = threadIdx.x & 63;
+    if (lane % (64 / NC) == 0) red[threadIdx.x >> 6][wave_component<NC>(lane)] = x;
+    __syncthreads();
+    if (threadIdx.x < NC)
+        out[threadIdx.x] = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+}
+
+// Sum v[0..count) (NC doubles each) in a fixed tree; the result is valid in thread 0.
+template <int NC>
+__device__ __forceinline__ void block_sum(const double *v, int count, double (&out)[NC], bool coherent)
+{
+    __shared__ double tot[NC][kBlock];
+    double s[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) s[k] = 0.0;
     for (int b = threadIdx.x; b < count; b += kBlock) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            s[k] += coherent ? __hip_atomic_load(&v[4 * b + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : v[4 * b + k];
+        for (int k = 0; k < NC; ++k)
+            s[k] += coherent ? __hip_atomic_load(&v[NC * b + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : v[NC * b + k];
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) tot[k][threadIdx.x] = s[k];
+    for (int k = 0; k < NC; ++k) tot[k][threadIdx.x] = s[k];
     __syncthreads();
     for (int w = kBlock / 2; w >= 1; w >>= 1) {
         if ((int)threadIdx.x < w) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) tot[k][threadIdx.x] += tot[k][threadIdx.x + w];
+            for (int k = 0; k < NC; ++k) tot[k][threadIdx.x] += tot[k][threadIdx.x + w];
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) out[k] = tot[k][0];
+    for (int k = 0; k < NC; ++k) out[k] = tot[k][0];
 }
 
-// block_sum4's sum computed by one wave alone, in exactly the same order
+// block_sum's sum computed by one wave alone, in exactly the same order
 // (bitwise the same result, valid in lane 0): lane l plays the threads l,
 // l + 64, l + 128 and l + 192 of the block (each first summing its strided
 // values), forms the tree's first two levels in registers, and takes the six
 // remaining levels with shuffles from the lane w above (no barriers).
-__device__ __forceinline__ void wave_sum4(const double *v, int count, double (&out)[4])
+// coherent: the values were written earlier in this launch.
+template <int NC>
+__device__ __forceinline__ void wave_sum(const double *v, int count, double (&out)[NC], bool coherent = false)
 {
     typedef double d2 __attribute__((ext_vector_type(2)));
     const int lane = threadIdx.x & 63;
-    double a[4][4];  // [block thread l + 64 q][component]
+    double a[4][NC];  // [block thread l + 64 q][component]
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) a[q][k] = 0.0;
+        for (int k = 0; k < NC; ++k) a[q][k] = 0.0;
     // one pass per 256 partials; the four threads' loads of a pass are
-    // independent and issued together (32 bytes each)
+    // independent and issued together
     for (int base = 0; base < count; base += kBlock) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int b = base + lane + 64 * q;
             if (b < count) {
-                const d2 lo = *reinterpret_cast<const d2 *>(v + 4 * (size_t)b);
-                const d2 hi = *reinterpret_cast<const d2 *>(v + 4 * (size_t)b + 2);
-                a[q][0] += lo[0];
-                a[q][1] += lo[1];
-                a[q][2] += hi[0];
-                a[q][3] += hi[1];
+                if (coherent) {
+#pragma unroll
+                    for (int k = 0; k < NC; ++k)
+                        a[q][k] += __hip_atomic_load(&v[NC * (size_t)b + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < NC; k += 2) {
+                        const d2 x = *reinterpret_cast<const d2 *>(v + NC * (size_t)b + k);
+                        a[q][k] += x[0];
+                        a[q][k + 1] += x[1];
+                    }
+                }
             }
         }
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < NC; ++k) {
         double x = (a[0][k] + a[2][k]) + (a[1][k] + a[3][k]);
 #pragma unroll
         for (int w = 32; w >= 1; w >>= 1) x += __shfl_down(x, w, 64);
@@ -692,37 +829,60 @@ __device__ __forceinline__ void wave_sum4(const double *v, int count, double (&o
     }
 }
 
+// {mass, momentum} of step number `step` from its summed parts, into the ring
+// (one thread).
+template <int NC>
+__device__ __forceinline__ void store_ring(const TotalsArgs &t, unsigned long long step, const double (&tot)[NC])
+{
+    double *r = t.ring + 4 * (step % kRingCap);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const double v = NC == 8 ? tot[k] + tot[NC - 4 + k] : tot[k];
+        r[k] = k == 0 ? t.n_fluid + v : v;
+    }
+}
+
 // The totals of one step from its workgroup partials t.partials, summed by a
 // single workgroup in the order of reduce_totals (each chunk of kRedChunk
 // partials, then the chunk sums, both in the same fixed trees, so the result
-// is bitwise the same) and appended to the ring.  The four waves take
-// chunks in turn.  The partials were written by an earlier launch, so no
-// fence is needed before reading them.
+// is bitwise the same) and appended to the ring.  The waves take chunks in
+// turn; the first wave sums the chunk sums.  The partials were written by an
+// earlier launch, so no fence is needed before reading them.
+template <int NC>
 __device__ __forceinline__ void append_step_totals(const TotalsArgs &t)
 {
     const int nchunks = (t.nparts + kRedChunk - 1) / kRedChunk;
-    for (int c = (int)threadIdx.x >> 6; c < nchunks; c += kBlock / 64) {
-        double gs[4];
-        wave_sum4(t.partials + 4 * (size_t)c * kRedChunk, min(kRedChunk, t.nparts - c * kRedChunk), gs);
+    for (int c = (int)threadIdx.x >> 6; c < nchunks; c += (int)blockDim.x >> 6) {
+        double gs[NC];
+        wave_sum<NC>(t.partials + NC * (size_t)c * kRedChunk, min(kRedChunk, t.nparts - c * kRedChunk), gs);
         if ((threadIdx.x & 63) == 0) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                __hip_atomic_store(&t.gpartials[4 * c + k], gs[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int k = 0; k < NC; ++k)
+                __hip_atomic_store(&t.gpartials[NC * c + k], gs[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __syncthreads();  // every wave's chunk sums are stored
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    double tot[4];
-    block_sum4(t.gpartials, nchunks, tot, true);
-    if (threadIdx.x == 0) {
-        const unsigned long long step = __hip_atomic_load(t.step_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        double *r = t.ring + 4 * (step % kRingCap);
-        r[0] = t.n_fluid + tot[0];
-        r[1] = tot[1];
-        r[2] = tot[2];
-        r[3] = tot[3];
-        __hip_atomic_store(t.step_counter, step + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x < 64) {
+        double tot[NC];
+        wave_sum<NC>(t.gpartials, nchunks, tot, true);
+        if (threadIdx.x == 0) {
+            const unsigned long long step = __hip_atomic_load(t.step_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            store_ring<NC>(t, step, tot);
+            __hip_atomic_store(t.step_counter, step + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+}
+
+// The totals of the n (1 or 2) steps of the previous launch, in order.
+template <int NC>
+__device__ __forceinline__ void append_prev_totals(int n, const TotalsArgs (&prev)[2])
+{
+    append_step_totals<NC>(prev[0]);
+    if (n > 1) {
+        __syncthreads();  // the chunk sums are rewritten
+        append_step_totals<NC>(prev[1]);
     }
 }
 
@@ -1091,28 +1251,11 @@ __device__ __forceinline__ uint32_t gather(const StepArgs &a, const char *src, c
     return dead;
 }
 
-// Collision constants of one site whose x-force is fx (the per-site force
-// field added to the uniform one); y and z forces stay uniform.
-__device__ __forceinline__ Coll coll_at(const Coll &p, float fx)
-{
-    Coll q = p;
-    q.fx = fx;
-    q.hfx = 0.5f * fx;
-#pragma unroll
-    for (int i = 1; i < kQ; ++i) {
-        const float cF = (float)CX[i] * fx + (float)CY[i] * p.fy + (float)CZ[i] * p.fz;
-        const float g3 = weight_class(i) == 1 ? p.g31 : p.g32;  // 3 (1 - omega/2) w_i
-        q.hC[i] = 3.0f * g3 * cF;
-        q.hD[i] = g3 * cF;
-    }
-    return q;
-}
-
 // Collide the V sites of a lane in place (loaded vectors in, values to store
 // out), with their moments in mr/mu/mv/mw.  kFField: site e's x-force is the
 // uniform one plus fxs[e] (FP32 storage).  Every kernel that collides a lane
 // goes through here, so equal inputs give equal bits whichever kernel runs.
-template <int C, int NW, bool kFField>
+template <int C, int NW, int kFField>
 __device__ __forceinline__ void collide_sites(Lane<NW> (&d)[kQ], const Coll &cp, const Scale16 &sc, Range16 &rng,
                                               const float (&fxs)[NW * 4 / Codec<C>::kBytes],
                                               float (&mr)[NW * 4 / Codec<C>::kBytes],
@@ -1129,12 +1272,10 @@ __device__ __forceinline__ void collide_sites(Lane<NW> (&d)[kQ], const Coll &cp,
             float gg[kQ];
 #pragma unroll
             for (int i = 0; i < kQ; ++i) gg[i] = K::dec(d[i].w[e]);
-            if constexpr (kFField) {
-                const Coll q = coll_at(cp, cp.fx + fxs[e]);
-                collide(gg, q, mr[e], mu[e], mv[e], mw[e]);
-            } else {
+            if constexpr (kFField != 0)
+                collide<true, kFField>(gg, cp, mr[e], mu[e], mv[e], mw[e], cp.fx + fxs[e]);
+            else
                 collide(gg, cp, mr[e], mu[e], mv[e], mw[e]);
-            }
 #pragma unroll
             for (int i = 0; i < kQ; ++i) d[i].w[e] = K::enc(gg[i]);
         }
@@ -1204,9 +1345,9 @@ __device__ __forceinline__ void s16_flag(const StepArgs &a, const Range16 &r)
 // like solid sites and take no part in the totals.  kFField: the x-force of
 // each site is the uniform one plus a per-site field (a.fx_field).  kPullNT:
 // as in gather.
-template <int C, int NW, bool kSolids, bool kMacros, bool kPadded, bool kFField = false, bool kPullNT = false>
+template <int C, int NW, bool kSolids, bool kMacros, bool kPadded, int NC, bool kFField = false, bool kPullNT = false>
 __device__ __forceinline__ void tile_update(const StepArgs &a, const char *src, char *dst, int tile,
-                                            double (&acc)[4], EdgeLds &lds)
+                                            double (&acc)[NC], EdgeLds &lds)
 {
     using K = Codec<C>;
     constexpr int V = NW * 4 / K::kBytes;  // sites per lane
@@ -1224,7 +1365,8 @@ __device__ __forceinline__ void tile_update(const StepArgs &a, const char *src, 
     if constexpr (kFField) {
         load_masks<V>(reinterpret_cast<const uint32_t *>(a.fx_field) + g.s0, reinterpret_cast<uint32_t(&)[V]>(fxs));
     }
-    collide_sites<C, NW, kFField>(d, cp, a.sc, rng, fxs, mr, mu, mv, mw);
+    constexpr int kOrder = kSolids == (kMacros && NW == 1) ? 2 : 1;
+    collide_sites<C, NW, kFField ? kOrder : 0>(d, cp, a.sc, rng, fxs, mr, mu, mv, mw);
 
     if (g.active) {
         // Solid (and padding) sites hold zero in both arrays: they are
@@ -1263,7 +1405,7 @@ __device__ __forceinline__ void tile_update(const StepArgs &a, const char *src, 
             }
         }
         // totals of the values as stored (after rounding), fluid sites only
-        add_lane_totals<C, NW>(d, acc, a.sc);
+        add_lane_totals<C, NW, NC>(d, acc, a.sc, a.split);
     }
     if constexpr (C == kS16) s16_flag(a, rng);
 }

@@ -23,6 +23,14 @@ struct Scale16 {
     float dm[3], da[3], em[3];
 };
 
+// Splitting constants of FP32 totals (add_moments): 1.5 * 2^52 times the two
+// quanta of the lattice.
+struct TotalSplit {
+    double m1, m2;
+};
+
+TotalSplit total_split(uint64_t sites);
+
 struct Shift16 {
     int sh[3];  // per weight class: codes divided by 2^sh (widening the range)
 };
@@ -88,13 +96,15 @@ struct Coll {
 
 Coll make_coll(float omega, float fx, float fy, float fz);
 
+constexpr int kTickets = 3;       // one per step of a launch, one for the steps
 constexpr int kRedChunk = 256;   // step-workgroup partials summed by one reduce workgroup (one per thread)
 
 struct TotalsArgs {
-    const double *partials;   // 4 doubles per step workgroup
+    const double *partials;   // nc doubles per step workgroup
     int nparts;               // step workgroups
-    double *gpartials;        // 4 doubles per reduce workgroup
-    unsigned int *ticket;     // arrival counter, 0 between launches
+    int nc;                   // 4, or 8 where the moments are summed in two parts (FP32 lattices)
+    double *gpartials;        // nc doubles per reduce workgroup, for two steps
+    unsigned int *ticket;     // kTickets arrival counters, 0 between launches
     double *ring;             // kRingCap x 4 doubles
     unsigned long long *step_counter;
     double n_fluid;           // number of fluid sites (exact in a double)
@@ -126,14 +136,48 @@ struct StepArgs {
     int mom_rec;              // with macros: 1 = rho_out receives one record (rho, u_x, u_y, u_z) per
                               // site (4N floats, site order) and u_out is unused; then dst may be
                               // nullptr (the step writes its moments only)
-    double *partials;         // out: 4 doubles per workgroup
+    double *partials;         // out: 4 doubles per workgroup (split totals: 8)
+    TotalSplit split;         // totals in two parts, or m1 = 0: in one
     const float *fx_field;    // optional per-site x-force added to coll.fx (N floats, site order) or nullptr
-    TotalsArgs prev;          // prev.partials != nullptr: workgroup 0 also appends the totals of the
-                              // step whose partials these are (written by the previous launch) to the ring
+    int nprev;                // a workgroup also appends the totals of the nprev (0..2) steps of the previous
+    TotalsArgs prev[2];       // launch, whose partials it wrote, to the ring
+    int prev_own;             // set at the launch (prev_own_group): that is the launch's first workgroup, which does nothing
+                              // else (the grid is one larger than the tiles)
     Scale16 sc;               // kS16 only
     unsigned int *ovf;        // kS16 only: two flag words; this step ORs into ovf[par] bit c when a code
     int par;                  // of weight class c leaves its range, and skips (ORing bit 3 into ovf[par])
                               // when ovf[par ^ 1] is set
+};
+
+// Whether a launch of grid tiles that appends totals takes a workgroup of its
+// own for that: where the tiles are one round of workgroups (at most four on
+// each of 256 CUs).
+inline int prev_own_group(const StepArgs &a, int grid) { return a.nprev > 0 && grid <= 4 * 256 ? 1 : 0; }
+
+// Two steps of one lattice in one launch (lb_march_kernels.hip): tiles of 64
+// columns (x), rows planes (z) and chunk rows (y); the last ones of each axis
+// may be shorter.
+constexpr int kMarchRows = 13;  // most planes of a tile
+
+struct MarchShape {
+    int nxt, nyt, nzt;        // tiles along x, y and z
+    int rows, chunk;
+    bool use;                 // faster than two one-step launches
+};
+
+struct MarchArgs {
+    const void *src;
+    void *dst;
+    Layout lay;
+    int nx, ny, nz;
+    int nxt, nzt, ntiles;     // tiles along x and z, and in all
+    int rows, chunk;
+    Coll coll;
+    TotalSplit split;
+    float *rho_out, *u_out;   // density and velocity of the second step, or nullptr
+    double *partials[2];      // out, per step: 8 doubles per tile and plane
+    int nprev;                // the launch's first workgroup appends the totals of the nprev steps of the
+    TotalsArgs prev[2];       // previous launch (0: there is no such workgroup)
 };
 
 // One lattice of a batch.  The step arguments of domain d are s, with the
@@ -243,7 +287,10 @@ struct MacroArgs {
 // rows with 16- / 8- / 4-byte accesses per lane and population plane.
 hipError_t launch_step(int codec, int variant, bool solids, bool macros, const StepArgs &a, int grid,
                        hipStream_t s);
-hipError_t launch_totals(const TotalsArgs &a, hipStream_t s);
+// The totals of the 1 or 2 steps of the last launch of a run.
+hipError_t launch_totals(const TotalsArgs *a, int nsteps, hipStream_t s);
+MarchShape march_shape(int nx, int ny, int nz, int cus);
+hipError_t launch_march2(const MarchArgs &a, hipStream_t s);
 hipError_t launch_init(int codec, const InitArgs &a, hipStream_t s);
 hipError_t launch_macros(int codec, const MacroArgs &a, hipStream_t s);
 // Neighbour masks of a (nx, ny, nz) lattice stored with row pitch >= nx

@@ -22,6 +22,9 @@
 // stream: 8- or 16-byte loads and stores per lane and population, lanes along
 // x, the +-1 x-shift of the pulled rows exchanged between neighbouring lanes
 // with one DPP move, one workgroup per tile of 256 lanes, no matrix cores.
+#include <algorithm>
+#include <cmath>
+
 #include "lb_device.h"
 
 namespace lbm {
@@ -35,62 +38,81 @@ __global__ __launch_bounds__(kBlock) void zero_words(unsigned int *p, int n)
     if (i < n) p[i] = 0u;
 }
 
-// Workgroup g sums partials [g * kRedChunk, (g + 1) * kRedChunk) into
-// gpartials[g]; the last workgroup to finish sums the gpartials in order and
-// appends {mass, momentum} of the step to the ring.
-__global__ __launch_bounds__(kBlock) void reduce_totals(TotalsArgs a)
+// The totals of the 1 or 2 steps of the last launch of a run (step blockIdx.y).
+// Workgroup g, one wave, sums partials [g * kRedChunk, (g + 1) * kRedChunk)
+// into gpartials[g]; a step's last workgroup to finish sums the gpartials in
+// order and stores {mass, momentum} of the step in the ring; the last of
+// those advances the step counter.  (A wave's registers and shuffles instead
+// of a workgroup's LDS tree and its sixteen barriers: the same additions,
+// 5.2 -> 3.4 us for the few partials of a small lattice.)
+template <int NC>
+__global__ __launch_bounds__(64) void reduce_totals(TotalsArgs t0, TotalsArgs t1, int nsteps)
 {
-    __shared__ int is_last;
+    const int s = blockIdx.y;
+    const TotalsArgs &a = s == 0 ? t0 : t1;
     // kS16: a flagged step has no totals (it is redone)
     if (a.ovf != nullptr && __hip_atomic_load(a.ovf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) return;
+    const int nchunks = (a.nparts + kRedChunk - 1) / kRedChunk;
+    if ((int)blockIdx.x >= nchunks) return;
     const int first = blockIdx.x * kRedChunk;
     const int count = min(kRedChunk, a.nparts - first);
-    double gs[4];
-    block_sum4(a.partials + 4 * (size_t)first, count, gs, false);
-    if (threadIdx.x == 0) {
+    double gs[NC];
+    wave_sum<NC>(a.partials + NC * (size_t)first, count, gs);
+    if (nchunks > 1) {
+        double *gp = a.gpartials + NC * (size_t)(s * gridDim.x);
+        unsigned int prev = 0;
+        if (threadIdx.x == 0) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            __hip_atomic_store(&a.gpartials[4 * blockIdx.x + k], gs[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int k = 0; k < NC; ++k)
+                __hip_atomic_store(&gp[NC * blockIdx.x + k], gs[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __threadfence();
+            prev = atomicAdd(&a.ticket[s], 1u);
+        }
+        if (__builtin_amdgcn_readfirstlane(prev) != (unsigned int)nchunks - 1) return;
         __threadfence();
-        const unsigned int prev = atomicAdd(a.ticket, 1u);
-        is_last = (prev == gridDim.x - 1);
+        wave_sum<NC>(gp, nchunks, gs, true);
     }
-    __syncthreads();
-    if (!is_last) return;
-    __threadfence();
-    double tot[4];
-    block_sum4(a.gpartials, gridDim.x, tot, true);
-    if (threadIdx.x == 0) {
-        const unsigned long long step = __hip_atomic_load(a.step_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        double *r = a.ring + 4 * (step % kRingCap);
-        r[0] = a.n_fluid + tot[0];
-        r[1] = tot[1];
-        r[2] = tot[2];
-        r[3] = tot[3];
-        __hip_atomic_store(a.step_counter, step + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(a.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x != 0) return;
+    const unsigned long long step = __hip_atomic_load(a.step_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    store_ring<NC>(a, step + s, gs);
+    __hip_atomic_store(&a.ticket[s], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (nsteps > 1) {
+        // the step counter was read above before the other step can advance it
+        __threadfence();
+        if (atomicAdd(&a.ticket[2], 1u) != (unsigned int)nsteps - 1) return;
+        __hip_atomic_store(&a.ticket[2], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    __hip_atomic_store(a.step_counter, step + nsteps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One step of one lattice: one workgroup per tile (the grid is the tile
-// count); each workgroup stores the FP64 totals of its tile.  In a run
-// of steps, workgroup 0 also appends the previous step's totals to the ring
-// (a.prev), so a run needs one totals kernel at its end instead of one per
-// step.
-template <int C, int NW, bool kSolids, bool kMacros, bool kFField = false, bool kPullNT = false>
+// One step of one lattice: one workgroup per tile; each stores the FP64
+// totals of its tile.  In a run of steps (a.prev) a workgroup also appends
+// the previous step's totals to the ring, so a run needs one totals kernel at
+// its end instead of one per step: on small grids a workgroup of its own, the
+// first (prev_own: as the tail of a tile's workgroup the append, 1-2 us, lies
+// on the critical path of a launch that is one round of workgroups; 32^3 step
+// 8.7 -> 7.5 us), on large ones that of the first tile.
+template <int C, int NW, bool kSolids, bool kMacros, int NC, bool kFField = false, bool kPullNT = false>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(vec_waves<C, NW>()))) void step_vec(StepArgs a)
 {
     __shared__ EdgeLds lds;
     if (s16_skip<C>(a)) return;
+    int b = blockIdx.x;
+    if (a.prev_own && b-- == 0) {
+        append_prev_totals<NC>(a.nprev, a.prev);
+        return;
+    }
     const char *src = reinterpret_cast<const char *>(a.src);
     char *dst = reinterpret_cast<char *>(a.dst);
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    double acc[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) acc[k] = 0.0;
     const int ntiles = (a.nslots + kBlock - 1) / kBlock;
-    if ((int)blockIdx.x < ntiles)
-        tile_update<C, NW, kSolids, kMacros, false, kFField, kPullNT>(a, src, dst,
-                                                                      tile_of(blockIdx.x, ntiles, a.tile_order), acc, lds);
-    store_block_totals(acc, a.partials + 4 * (size_t)blockIdx.x);
-    if (a.prev.partials != nullptr && blockIdx.x == 0) append_step_totals(a.prev);
+    if (b < ntiles)
+        tile_update<C, NW, kSolids, kMacros, false, NC, kFField, kPullNT>(a, src, dst, tile_of(b, ntiles, a.tile_order),
+                                                                          acc, lds);
+    store_block_totals<NC>(acc, a.partials + NC * (size_t)b);
+    if (a.nprev > 0 && !a.prev_own && b == 0) append_prev_totals<NC>(a.nprev, a.prev);
 }
 
 // ---------------------------------------------- step: one site per thread --
@@ -105,7 +127,10 @@ __global__ __launch_bounds__(kBlock) void step_site(StepArgs a)
     const uint32_t nx = (uint32_t)a.nx, ny = (uint32_t)a.ny, nz = (uint32_t)a.nz;
     const char *src = reinterpret_cast<const char *>(a.src);
     char *dst = reinterpret_cast<char *>(a.dst);
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    constexpr int NC = 4;
+    double acc[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) acc[k] = 0.0;
     const int ntiles = (a.nslots + kBlock - 1) / kBlock;
     Range16 rng;  // kS16: range test of the codes
 
@@ -157,13 +182,10 @@ __global__ __launch_bounds__(kBlock) void step_site(StepArgs a)
         }
         double m, px, py, pz;
         moments_of_totals(tot, m, px, py, pz);
-        acc[0] += m;
-        acc[1] += px;
-        acc[2] += py;
-        acc[3] += pz;
+        add_moments<NC>(m, px, py, pz, acc, a.split);
     }
     if constexpr (C == kS16) s16_flag(a, rng);
-    store_block_totals(acc, a.partials + 4 * (size_t)blockIdx.x);
+    store_block_totals<NC>(acc, a.partials + NC * (size_t)blockIdx.x);
 }
 
 // Solid sites get zero macros in the one-site kernel (it skips them).
@@ -448,36 +470,39 @@ __global__ __launch_bounds__(kBlock) void copy16(const u32x4 *src, u32x4 *dst, u
     }
 }
 
-template <int C, bool S, bool M>
+template <int C, bool S, bool M, int NC = 4>
 void *step_fn(int variant)
 {
-    if (variant == 1) return reinterpret_cast<void *>(&step_vec<C, 4, S, M>);
-    if (variant == 2) return reinterpret_cast<void *>(&step_vec<C, 2, S, M>);
-    if (variant == 3) return reinterpret_cast<void *>(&step_vec<C, 1, S, M>);
+    if (variant == 1) return reinterpret_cast<void *>(&step_vec<C, 4, S, M, NC>);
+    if (variant == 2) return reinterpret_cast<void *>(&step_vec<C, 2, S, M, NC>);
+    if (variant == 3) return reinterpret_cast<void *>(&step_vec<C, 1, S, M, NC>);
     return reinterpret_cast<void *>(&step_site<C, S, M>);
 }
 
 template <bool S, bool M>
 void *ffield_fn(int variant)
 {
-    if (variant == 1) return reinterpret_cast<void *>(&step_vec<kF32, 4, S, M, true>);
-    if (variant == 2) return reinterpret_cast<void *>(&step_vec<kF32, 2, S, M, true>);
-    return reinterpret_cast<void *>(&step_vec<kF32, 1, S, M, true>);
+    if (variant == 1) return reinterpret_cast<void *>(&step_vec<kF32, 4, S, M, 4, true>);
+    if (variant == 2) return reinterpret_cast<void *>(&step_vec<kF32, 2, S, M, 4, true>);
+    return reinterpret_cast<void *>(&step_vec<kF32, 1, S, M, 4, true>);
 }
 
 // Plain steps of lattices with solids, pulling with non-temporal loads.
 template <int C>
 void *pull_nt_fn(int variant)
 {
-    if (variant == 1) return reinterpret_cast<void *>(&step_vec<C, 4, true, false, false, true>);
-    if (variant == 2) return reinterpret_cast<void *>(&step_vec<C, 2, true, false, false, true>);
-    return reinterpret_cast<void *>(&step_vec<C, 1, true, false, false, true>);
+    if (variant == 1) return reinterpret_cast<void *>(&step_vec<C, 4, true, false, 4, false, true>);
+    if (variant == 2) return reinterpret_cast<void *>(&step_vec<C, 2, true, false, 4, false, true>);
+    return reinterpret_cast<void *>(&step_vec<C, 1, true, false, 4, false, true>);
 }
 
 // pull_nt: plain steps with solids on the vector-row kernels pull with
-// non-temporal loads (ignored elsewhere)
-void *pick_step(int codec, int variant, bool solids, bool macros, bool ffield, bool pull_nt = false)
+// non-temporal loads (ignored elsewhere).  split: totals in two parts (FP32
+// without solids; ignored on the one-site kernel and with a force field).
+void *pick_step(int codec, int variant, bool solids, bool macros, bool ffield, bool pull_nt = false, bool split = false)
 {
+    if (split && !ffield && variant != 0)
+        return macros ? step_fn<kF32, false, true, 8>(variant) : step_fn<kF32, false, false, 8>(variant);
     if (pull_nt && solids && !macros && !ffield && variant != 0) {
         switch (codec) {
             case kF32: return pull_nt_fn<kF32>(variant);
@@ -530,6 +555,19 @@ Coll make_coll(float omega, float fx, float fy, float fz)
     return p;
 }
 
+// Quanta of the two parts of FP32 totals on a lattice of n sites: the sums
+// of up to n first parts of magnitude at most 4, and of n second parts of at
+// most half the first quantum, stay below 2^53 of their quanta (exact).
+// Larger moments (a blown-up state) only lose the independence of the order,
+// not accuracy.
+TotalSplit total_split(uint64_t n)
+{
+    int lg = 0;
+    while ((1ull << lg) < n) ++lg;
+    const int e1 = lg + 2 - 53, e2 = (e1 - 1) + lg - 53;
+    return TotalSplit{std::ldexp(1.5, 52 + e1), std::ldexp(1.5, 52 + e2)};
+}
+
 int sites_per_thread(int codec, int variant)
 {
     const int nw = variant == 1 ? 4 : (variant == 2 ? 2 : (variant == 3 ? 1 : 0));
@@ -548,10 +586,12 @@ int step_occupancy(int codec, int variant, bool solids, bool macros)
 
 hipError_t launch_step(int codec, int variant, bool solids, bool macros, const StepArgs &a, int grid, hipStream_t s)
 {
-    void *fn = pick_step(codec, variant, solids, macros, a.fx_field != nullptr, a.pull_nt != 0);
+    void *fn = pick_step(codec, variant, solids, macros, a.fx_field != nullptr, a.pull_nt != 0,
+                         a.split.m1 != 0.0);
     StepArgs arg = a;
+    arg.prev_own = prev_own_group(a, grid);
     void *params[] = {&arg};
-    return hipLaunchKernel(fn, dim3(grid), dim3(kBlock), params, 0, s);
+    return hipLaunchKernel(fn, dim3(grid + arg.prev_own), dim3(kBlock), params, 0, s);
 }
 
 hipError_t launch_repack(void *planes, void *state, const Layout &lay, int64_t n, int esize, bool to_state,
@@ -582,10 +622,15 @@ hipError_t launch_aa_planes(void *planes, void *state, const Layout &lay, int ny
     return hipGetLastError();
 }
 
-hipError_t launch_totals(const TotalsArgs &a, hipStream_t s)
+hipError_t launch_totals(const TotalsArgs *a, int nsteps, hipStream_t s)
 {
-    const int g = (a.nparts + kRedChunk - 1) / kRedChunk;
-    reduce_totals<<<g, kBlock, 0, s>>>(a);
+    int g = 1;
+    for (int k = 0; k < nsteps; ++k) g = std::max(g, (a[k].nparts + kRedChunk - 1) / kRedChunk);
+    const TotalsArgs &t0 = a[0], &t1 = a[nsteps - 1];
+    if (t0.nc == 8)
+        reduce_totals<8><<<dim3(g, nsteps), 64, 0, s>>>(t0, t1, nsteps);
+    else
+        reduce_totals<4><<<dim3(g, nsteps), 64, 0, s>>>(t0, t1, nsteps);
     return hipGetLastError();
 }
 
