@@ -39,6 +39,9 @@ struct lb2d_lattice {
     unsigned long long *counter = nullptr;
     hipStream_t stream = nullptr;
     int variant = 1, vsites = 4, grid = 1;
+    March2Shape march[kMaxSteps + 1] = {};  // of launches of 2 and 4 steps
+    int most = 1;                           // most steps of one launch
+    size_t parts = 1;                       // partials of one of a run's two buffers
     long long steps = 0;
 };
 
@@ -85,17 +88,17 @@ Step2Args step2_args(const lb2d_lattice *h, int from)
     }
     a.nbmask = h->nbmask;
     a.chunkdirty = h->chunkdirty;
-    a.partials = h->partials;
+    a.split = total_split(h->n);
     return a;
 }
 
-// Totals of the step whose workgroup partials are in buffer buf (0 or 1).
-TotalsArgs totals2(const lb2d_lattice *h, int buf)
+// Totals of a step whose nparts partials start at partials.
+TotalsArgs totals2(const lb2d_lattice *h, const double *partials, int nparts)
 {
     TotalsArgs t{};
-    t.nc = 4;
-    t.partials = h->partials + (size_t)buf * 4 * h->grid;
-    t.nparts = h->grid;
+    t.nc = 8;
+    t.partials = partials;
+    t.nparts = nparts;
     t.gpartials = h->gpartials;
     t.ticket = h->ticket;
     t.ring = h->ring;
@@ -104,24 +107,44 @@ TotalsArgs totals2(const lb2d_lattice *h, int buf)
     return t;
 }
 
-// n steps as one run: step k writes its workgroup partials into buffer k & 1
-// and the first workgroup of step k + 1 appends the totals of step k; one
-// totals kernel closes the run (the ring holds the same values as with one
-// totals kernel per step).
+// n steps as one run of launches of four, two or one steps: a launch writes
+// its steps' partials into one of two buffers in turn, a workgroup of the next
+// launch appends their totals, and one totals kernel closes the run (the ring
+// holds the same values as with a totals kernel after every step).
 int enqueue2(lb2d_lattice *h, int n)
 {
-    for (int k = 0; k < n; ++k) {
+    TotalsArgs prev[kMaxSteps];
+    int nprev = 0;
+    for (int launch = 0; n > 0; ++launch) {
+        int steps = 1;
+        while (2 * steps <= std::min(n, h->most)) steps *= 2;
+        double *buf = h->partials + (size_t)(launch & 1) * 8 * h->parts;
         Step2Args a = step2_args(h, h->cur);
-        a.partials = h->partials + (size_t)(k & 1) * 4 * h->grid;
-        if (k > 0) a.prev = totals2(h, (k - 1) & 1);
-        HIP_OR_FAIL(launch_step2d(h->variant, h->solids, a, h->grid, h->stream));
+        a.nprev = nprev;
+        std::copy(prev, prev + nprev, a.prev);
+        if (steps == 1) {
+            a.partials = buf;
+            HIP_OR_FAIL(launch_step2d(h->variant, h->solids, a, h->grid, h->stream));
+            prev[0] = totals2(h, buf, h->grid);
+        } else {
+            const March2Shape &p = h->march[steps];
+            March2Args m{};
+            m.s = a;
+            m.nstrips = p.nstrips;
+            m.chunk = p.chunk;
+            m.nitems = p.nitems;
+            for (int k = 0; k < steps; ++k) {
+                m.partials[k] = buf + (size_t)k * 8 * p.nitems;
+                prev[k] = totals2(h, m.partials[k], p.nitems);
+            }
+            HIP_OR_FAIL(launch_march2d(h->variant, steps, h->solids, m, h->stream));
+        }
+        nprev = steps;
         h->cur ^= 1;
-        h->steps += 1;
+        h->steps += steps;
+        n -= steps;
     }
-    if (n > 0) {
-        const TotalsArgs t = totals2(h, (n - 1) & 1);
-        HIP_OR_FAIL(launch_totals(&t, 1, h->stream));
-    }
+    if (nprev > 0) HIP_OR_FAIL(launch_totals(prev, nprev, h->stream));
     return LB_OK;
 }
 
@@ -198,6 +221,28 @@ lb2d_lattice *lb2d_create(int nx, int ny, double tau, const uint8_t *flags, doub
     h->arr_elems = ((uint64_t)ny + R - 1) / R * h->lay.blk;
     const uint64_t tiles = (n / h->vsites + kBlock - 1) / kBlock;
     h->grid = (int)std::min<uint64_t>(tiles, 0x7fffffffull);  // one workgroup per tile
+    h->parts = (size_t)h->grid;
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+        delete h;
+        fail(LB_EHIP, "hipGetDevice");
+        return nullptr;
+    }
+    // Steps of one launch: the most that the estimate says pays, a step2d launch
+    // taking 5.5 us (9.3 at least) and its bytes at 6.5 TB/s.  Measured a step,
+    // one / two / four: 128^2 9.6 / 6.5 / 8.5, 1024^2 17.0 / 14.7 / 15.6, 2048^2
+    // 53 / 35 / 29, 4096^2 192 / 116 / 80.  (LB_STEPS2D = 1, 2 or 4 instead.)
+    const long forced = env_long("LB_STEPS2D", 0);
+    double step_us = std::max(9.3, 5.5 + (double)n * 72.0 / 6.5e6);
+    for (int k = 2; k <= kMaxSteps; k *= 2) {
+        h->march[k] = march2_shape(h->variant, k, nx, ny, cus);
+        if (forced ? k <= forced : h->march[k].us / k < step_us) {
+            step_us = h->march[k].us / k;
+            h->most = k;
+        }
+    }
+    for (int k = 2; k <= h->most; k *= 2) h->parts = std::max(h->parts, (size_t)k * h->march[k].nitems);
 
     auto bail = [&](int code, const char *what, hipError_t e) -> lb2d_lattice * {
         release2(h);
@@ -211,9 +256,9 @@ lb2d_lattice *lb2d_create(int nx, int ny, double tau, const uint8_t *flags, doub
         if ((e = hipMalloc(&h->buf[b], bytes)) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc(populations)", e);
         if ((e = hipMemsetAsync(h->buf[b], 0, bytes, h->stream)) != hipSuccess) return bail(LB_EHIP, "hipMemsetAsync", e);
     }
-    const size_t ngroups = ((size_t)h->grid + kRedChunk - 1) / kRedChunk;
-    if ((e = hipMalloc(&h->partials, (size_t)h->grid * 8 * sizeof(double))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
-    if ((e = hipMalloc(&h->gpartials, ngroups * 4 * sizeof(double))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
+    const size_t ngroups = (h->parts + kRedChunk - 1) / kRedChunk;
+    if ((e = hipMalloc(&h->partials, h->parts * 2 * 8 * sizeof(double))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
+    if ((e = hipMalloc(&h->gpartials, ngroups * kMaxSteps * 8 * sizeof(double))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
     if ((e = hipMalloc(&h->ring, (size_t)kRingCap * 4 * sizeof(double))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
     if ((e = hipMalloc(&h->ticket, kTickets * sizeof(unsigned int))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);
     if ((e = hipMalloc(&h->counter, sizeof(unsigned long long))) != hipSuccess) return bail(LB_ENOMEM, "hipMalloc", e);

@@ -875,14 +875,13 @@ __device__ __forceinline__ void append_step_totals(const TotalsArgs &t)
     }
 }
 
-// The totals of the n (1 or 2) steps of the previous launch, in order.
-template <int NC>
-__device__ __forceinline__ void append_prev_totals(int n, const TotalsArgs (&prev)[2])
+// The totals of the n (1..M) steps of the previous launch, in order.
+template <int NC, int M>
+__device__ __forceinline__ void append_prev_totals(int n, const TotalsArgs (&prev)[M])
 {
-    append_step_totals<NC>(prev[0]);
-    if (n > 1) {
-        __syncthreads();  // the chunk sums are rewritten
-        append_step_totals<NC>(prev[1]);
+    for (int k = 0; k < n; ++k) {
+        if (k > 0) __syncthreads();  // the chunk sums are rewritten
+        append_step_totals<NC>(prev[k]);
     }
 }
 

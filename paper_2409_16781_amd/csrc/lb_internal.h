@@ -96,14 +96,15 @@ struct Coll {
 
 Coll make_coll(float omega, float fx, float fy, float fz);
 
-constexpr int kTickets = 3;       // one per step of a launch, one for the steps
+constexpr int kMaxSteps = 4;      // most steps of one launch
+constexpr int kTickets = kMaxSteps + 1;  // one per step of a launch, one for the steps
 constexpr int kRedChunk = 256;   // step-workgroup partials summed by one reduce workgroup (one per thread)
 
 struct TotalsArgs {
     const double *partials;   // nc doubles per step workgroup
     int nparts;               // step workgroups
     int nc;                   // 4, or 8 where the moments are summed in two parts (FP32 lattices)
-    double *gpartials;        // nc doubles per reduce workgroup, for two steps
+    double *gpartials;        // nc doubles per reduce workgroup, for each step of a launch
     unsigned int *ticket;     // kTickets arrival counters, 0 between launches
     double *ring;             // kRingCap x 4 doubles
     unsigned long long *step_counter;
@@ -252,8 +253,23 @@ struct Step2Args {
     float lidc[9];            // 6 w_i (c_i . u_lid): added to a value bounced off the lid
     const uint32_t *nbmask;   // bit i: site x - c_i solid; bit 8 + i: that site is the lid; bit 31: own solid
     const uint8_t *chunkdirty;  // per 64 sites (site s in chunk s / 64): any mask bit set
-    double *partials;         // 4 doubles per workgroup (mass, px, py, 0)
-    TotalsArgs prev;          // as in StepArgs: the previous step's totals appended by workgroup 0
+    TotalSplit split;
+    double *partials;         // 8 doubles per workgroup (mass, px, py, 0 in two parts)
+    int nprev;                // a workgroup also appends the totals of the nprev steps of the previous launch
+    TotalsArgs prev[kMaxSteps];
+};
+
+// Several steps of a D2Q9 lattice in one launch (march2d): strips of columns,
+// chunks of rows, one wave each.
+struct March2Args {
+    Step2Args s;              // partials unused
+    int nstrips, chunk, nitems;
+    double *partials[kMaxSteps];  // out, per step: 8 doubles per item
+};
+
+struct March2Shape {
+    int nstrips, chunk, nitems;
+    double us;                // estimated time of a launch
 };
 
 // The reduction of one step's partials into the ring of per-step totals.
@@ -348,6 +364,9 @@ hipError_t launch_aa_step(int codec, int variant, bool solids, bool from_even, c
 int aa_occupancy(int codec, int variant, bool solids, bool from_even);
 // D2Q9: variant 1 / 2 / 3 = 4 / 2 / 1 sites per lane (FP32 storage).
 hipError_t launch_step2d(int variant, bool solids, const Step2Args &a, int grid, hipStream_t s);
+// steps (2 or 4) steps in one launch of the shape march2_shape gives.
+March2Shape march2_shape(int variant, int steps, int nx, int ny, int cus);
+hipError_t launch_march2d(int variant, int steps, bool solids, const March2Args &a, hipStream_t s);
 // D2Q9 masks (nx * ny, site order) and one dirty byte per 64 sites ((n + 63) / 64 bytes).
 hipError_t launch_masks2d(const uint8_t *flags, int nx, int ny, uint32_t *nbmask, uint8_t *chunkdirty, hipStream_t s);
 hipError_t launch_init2d(void *dst, const Layout &lay, int nx, int ny, const double *rho, const double *u,

@@ -38,7 +38,11 @@ __global__ __launch_bounds__(kBlock) void zero_words(unsigned int *p, int n)
     if (i < n) p[i] = 0u;
 }
 
-// The totals of the 1 or 2 steps of the last launch of a run (step blockIdx.y).
+struct TotalsList {
+    TotalsArgs t[kMaxSteps];
+};
+
+// The totals of the steps of the last launch of a run (step blockIdx.y).
 // Workgroup g, one wave, sums partials [g * kRedChunk, (g + 1) * kRedChunk)
 // into gpartials[g]; a step's last workgroup to finish sums the gpartials in
 // order and stores {mass, momentum} of the step in the ring; the last of
@@ -46,10 +50,10 @@ __global__ __launch_bounds__(kBlock) void zero_words(unsigned int *p, int n)
 // of a workgroup's LDS tree and its sixteen barriers: the same additions,
 // 5.2 -> 3.4 us for the few partials of a small lattice.)
 template <int NC>
-__global__ __launch_bounds__(64) void reduce_totals(TotalsArgs t0, TotalsArgs t1, int nsteps)
+__global__ __launch_bounds__(64) void reduce_totals(TotalsList list, int nsteps)
 {
     const int s = blockIdx.y;
-    const TotalsArgs &a = s == 0 ? t0 : t1;
+    const TotalsArgs &a = list.t[s];
     // kS16: a flagged step has no totals (it is redone)
     if (a.ovf != nullptr && __hip_atomic_load(a.ovf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) return;
     const int nchunks = (a.nparts + kRedChunk - 1) / kRedChunk;
@@ -77,10 +81,10 @@ __global__ __launch_bounds__(64) void reduce_totals(TotalsArgs t0, TotalsArgs t1
     store_ring<NC>(a, step + s, gs);
     __hip_atomic_store(&a.ticket[s], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (nsteps > 1) {
-        // the step counter was read above before the other step can advance it
+        // the step counter was read above before another step can advance it
         __threadfence();
-        if (atomicAdd(&a.ticket[2], 1u) != (unsigned int)nsteps - 1) return;
-        __hip_atomic_store(&a.ticket[2], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (atomicAdd(&a.ticket[kMaxSteps], 1u) != (unsigned int)nsteps - 1) return;
+        __hip_atomic_store(&a.ticket[kMaxSteps], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __hip_atomic_store(a.step_counter, step + nsteps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -626,11 +630,12 @@ hipError_t launch_totals(const TotalsArgs *a, int nsteps, hipStream_t s)
 {
     int g = 1;
     for (int k = 0; k < nsteps; ++k) g = std::max(g, (a[k].nparts + kRedChunk - 1) / kRedChunk);
-    const TotalsArgs &t0 = a[0], &t1 = a[nsteps - 1];
-    if (t0.nc == 8)
-        reduce_totals<8><<<dim3(g, nsteps), 64, 0, s>>>(t0, t1, nsteps);
+    TotalsList list{};
+    std::copy(a, a + nsteps, list.t);
+    if (a[0].nc == 8)
+        reduce_totals<8><<<dim3(g, nsteps), 64, 0, s>>>(list, nsteps);
     else
-        reduce_totals<4><<<dim3(g, nsteps), 64, 0, s>>>(t0, t1, nsteps);
+        reduce_totals<4><<<dim3(g, nsteps), 64, 0, s>>>(list, nsteps);
     return hipGetLastError();
 }
 
