@@ -82,6 +82,7 @@ struct lb_lattice {
     void *alloc[2];   // allocations holding buf[0], buf[1] (buf[b] may sit at an offset)
     int cur;          // buf[cur] holds the state
     uint8_t *flags;   // device copy, or nullptr when all fluid
+    int auto_variant; // variant, if it is the default one for the lattice (0: tuned or set)
     float *ffield;    // per-site x-force added to force[0] (device, N floats), or nullptr
     uint32_t *nbmask;
     uint8_t *rowdirty;
@@ -146,6 +147,8 @@ StepArgs step_args(const lb_lattice *h, int from, float *rho, float *u, int vari
     const int row_lanes = h->nx / vsites;
     a.tile_order = h->tile_order;
     a.pull_nt = h->pull_nt;
+    // the rounding of the width that was the only default, for any nx it fits
+    a.rest_once = h->auto_variant != 0 && h->nx % 8 == 0;
     a.lds_edges = (variant != 0 && (h->inplace || env_long("LB_LDS_EDGES", 1) != 0)) ? 1 : 0;
     a.lg_row_lanes = 0;
     while ((1 << a.lg_row_lanes) < row_lanes) ++a.lg_row_lanes;
@@ -603,6 +606,17 @@ int alloc_partials(lb_lattice *h, size_t parts)
     return LB_OK;
 }
 
+// Step kernel of another vector width (the stream's work is waited for).
+int set_variant(lb_lattice *h, int variant)
+{
+    if (variant == h->variant) return LB_OK;
+    HIP_OR_FAIL(hipStreamSynchronize(h->stream));
+    h->variant = variant;
+    h->vsites = sites_per_thread(h->codec, variant);
+    h->grid = (int)std::min<uint64_t>((h->n / h->vsites + kBlock - 1) / kBlock, 0x7fffffffull);
+    return alloc_partials(h, buf_parts(h));
+}
+
 void release(lb_lattice *h)
 {
     h->graphs.release();
@@ -616,6 +630,47 @@ void release(lb_lattice *h)
     if (h->adj_mom) (void)hipFree(h->adj_mom);
     h->adj_mom = nullptr;
     h->adj_mom_steps = 0;
+}
+
+// Vector width of the step kernel for a lattice of n sites (1, 2, 3: 16-, 8- and
+// 4-byte vectors).  Fewer sites a lane are more workgroups for a small lattice,
+// more of them at a time, and fewer values behind a bounced one; more sites a
+// lane are fewer accesses for the same bytes.  Measured, microseconds a step
+// with 16- / 8- / 4-byte vectors:
+//   FP32      32^3 7.4 / 5.9 / 5.0, 64^3 11.1 / 10.1 / 11.3, 160^3 110 / 105 /
+//             107, 512^3 3217 / 3332 / 3326; with solids (spheres) 32^3 9.9 /
+//             9.0 / 5.2, 128^3 64.5 / 66.4 / 58.6, 256^3 500 / 539 / 567
+//   FP16      32^3 9.2 / 6.2 / 4.8, 128^3 32.6 / 31.0 / 29.2, 512^3 1654 /
+//             1608 / 1557; solids 32^3 17.5 / 12.5 / 10.2, 128^3 49.5 / 45.4 /
+//             50.3, 256^3 333 / 351 / 382
+//   BF16      as FP16, without solids 160^3 64.4 / 62.3 / 61.2, 200^3 115.0 /
+//             112.1 / 114.5
+//   scaled    32^3 11.7 / 7.7 / 5.6, 256^3 234 / 208 / 208, 512^3 1761 / 1596 /
+//             1613; solids 64^3 21.2 / 14.7 / 12.8, 160^3 123 / 109 / 106,
+//             256^3 429 / 375 / 393
+//   in place  FP32 32^3 8.5 / 7.0 / 6.4, 128^3 55.8 / 54.8 / 57.0, 256^3 400 /
+//             402 / 416; solids 256^3 1348 / 1484 / 602; 16-bit 64^3 10.6 / 8.2
+//             / 7.9, 256^3 204 / 200 / 207; solids 64^3 32 / 28 / 24, 256^3 947
+//             / 1005 / 1093
+// The upper bounds also keep the totals of every lattice that fits with
+// 16-byte vectors (scaled: 8-byte) within the scratch array of lb_step_noalloc.
+int default_variant(int storage, bool inplace, bool solids, uint64_t n)
+{
+    auto by_size = [n](int lg3, int lg2) { return n <= (1ull << lg3) ? 3 : (n <= (1ull << lg2) ? 2 : 1); };
+    if (inplace) {
+        if (storage == LB_F32) return solids ? by_size(25, 0) : by_size(16, 22);
+        if (storage == LB_F16S) return 1;
+        return solids ? by_size(18, 0) : by_size(18, 24);
+    }
+    // between 2^19 and 2^21 sites the 4-byte 16-bit kernels (512 sites a
+    // workgroup, five workgroups a CU) take one round and a short second one
+    const bool rounds = n <= (1ull << 19) || n >= (1ull << 21);
+    switch (storage) {
+        case LB_F32: return solids ? by_size(22, 0) : by_size(16, 23);
+        case LB_F16S: return solids ? by_size(18, 0) : (rounds ? by_size(26, 0) : 1);
+        case LB_S16: return solids ? by_size(20, 63) : by_size(21, 63);
+        default: return solids ? by_size(18, 23) : (rounds ? by_size(22, 27) : 1);
+    }
 }
 
 int create_impl(lb_lattice **out, int nx, int ny, int nz, double tau, const uint8_t *flags, int storage,
@@ -656,13 +711,11 @@ int create_impl(lb_lattice **out, int nx, int ny, int nz, double tau, const uint
     h->n_fluid = (double)(n - nsolid);
     h->inplace = inplace;
 
-    // Step kernel: vector rows with 16-byte accesses (FP32: 4 sites per lane,
-    // FP16/BF16: 8) or, for the scaled 16-bit codec, 8-byte accesses (4
-    // sites: its 16-byte kernel runs at two waves per SIMD); narrower vectors
-    // when nx is not a multiple of the width, one site per thread when no
-    // vector width divides nx.  LB_KERNEL (0..3) overrides the choice.
+    // Step kernel: vector rows (default_variant); narrower vectors when nx is
+    // not a multiple of the width, one site per thread when no vector width
+    // divides nx.  LB_KERNEL (0..3) overrides the choice.
     const long kernel = env_long("LB_KERNEL", -1);
-    int variant = storage == LB_S16 ? 2 : 1;
+    int variant = default_variant(storage, inplace, nsolid > 0, n);
     if (kernel >= 0 && kernel <= 3) variant = (int)kernel;
     else if (kernel != -1) {
         delete h;
@@ -686,6 +739,7 @@ int create_impl(lb_lattice **out, int nx, int ny, int nz, double tau, const uint
             return nx % V == 0 && nx / V <= kBlock && kBlock % (nx / V) == 0;
         };
         int v = variant == 0 ? 1 : variant;
+        if (kernel < 0 && !rows_fit(v)) v = 1;
         while (v <= 3 && !rows_fit(v)) ++v;
         if (v > 3) {
             delete h;
@@ -694,6 +748,7 @@ int create_impl(lb_lattice **out, int nx, int ny, int nz, double tau, const uint
         variant = v;
     }
     h->variant = variant;
+    h->auto_variant = kernel < 0 ? variant : 0;
     h->vsites = sites_per_thread(storage, h->variant);
     // Storage blocks of R rows: by default the largest power of two with
     // R * nx * bytes <= 32 KiB per population segment.  LB_BLOCK_ROWS (a power
@@ -973,7 +1028,7 @@ int lb_set_force_field(lb_lattice *h, const float *fx)
         if (h->ffield) (void)hipFree(h->ffield);
         h->ffield = nullptr;
         h->graphs.invalidate();
-        return LB_OK;
+        return h->auto_variant != 0 ? set_variant(h, h->auto_variant) : LB_OK;
     }
     if (h->codec != kF32) return fail(LB_EINVAL, "force fields need FP32 storage");
     if (h->inplace) return fail(LB_EINVAL, "force fields need two-array storage");
@@ -985,17 +1040,15 @@ int lb_set_force_field(lb_lattice *h, const float *fx)
         }
     }
     HIP_OR_FAIL(hipMemcpyAsync(h->ffield, fx, h->n * sizeof(float), hipMemcpyDeviceToDevice, h->stream));
-    // the field is read as whole vectors of the row kernels: any nx works with one site per lane
-    if (h->variant == 0) {
-        h->variant = 3;
-        h->vsites = sites_per_thread(h->codec, 3);
-        const uint64_t tiles = (h->n / h->vsites + kBlock - 1) / kBlock;
-        h->grid = (int)std::min<uint64_t>(tiles, 0x7fffffffull);
-        HIP_OR_FAIL(hipStreamSynchronize(h->stream));
-        if (int rc = alloc_partials(h, buf_parts(h))) return rc;
-    }
+    // the field is read as whole vectors of the row kernels: any nx works with
+    // one site per lane.  A lattice of default width takes the widest vectors:
+    // the one-site kernels with and without field output round j.u in another
+    // order, and a gradient must not depend on its checkpoints.
+    int v = h->variant == 0 ? 3 : h->variant;
+    if (h->auto_variant != 0)
+        for (v = 1; h->nx % sites_per_thread(h->codec, v) != 0;) ++v;
     h->graphs.invalidate();
-    return LB_OK;
+    return set_variant(h, v);
 }
 
 }  // extern "C"
@@ -1457,6 +1510,7 @@ int lb_tune(lb_lattice *h, int reps)
     for (const Cand &c : cands)
         if (c.ms < best->ms) best = &c;
     h->variant = best->variant;
+    h->auto_variant = 0;
     h->vsites = sites_per_thread(h->codec, best->variant);
     h->tile_order = best->order;
     h->pull_nt = best->nt;

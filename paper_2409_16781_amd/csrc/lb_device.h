@@ -992,6 +992,18 @@ constexpr int vec_waves()
 #endif
 }
 
+// Most waves per SIMD of a step kernel (8: as many as fit).  Few more waves
+// than it takes to hide a load make the caches' working set larger than what
+// is reused: one vector word a lane runs faster at five waves with 16-bit
+// storage (256^3 in FP16 198 -> 194 us a step, scaled 16-bit 211 -> 205;
+// 256x128x128 channel in FP16 59.9 -> 57.4) and at six with a force field
+// (128^3 57.6 -> 56.9).
+template <int C, int NW, bool kFField>
+constexpr int most_waves()
+{
+    return NW == 1 ? (Codec<C>::kBytes == 2 ? 5 : (kFField ? 6 : 8)) : 8;
+}
+
 // Workgroups are dispatched round-robin over the chip's 8 XCDs (workgroup b
 // runs on XCD b mod 8).  Order 1 gives each XCD a contiguous range of tiles:
 // a bijection of [0, ntiles) that leaves the last ntiles mod 8 tiles in place.
@@ -1254,7 +1266,11 @@ __device__ __forceinline__ uint32_t gather(const StepArgs &a, const char *src, c
 // out), with their moments in mr/mu/mv/mw.  kFField: site e's x-force is the
 // uniform one plus fxs[e] (FP32 storage).  Every kernel that collides a lane
 // goes through here, so equal inputs give equal bits whichever kernel runs.
-template <int C, int NW, int kFField>
+// The exception is the rest population in FP16, which ends in a fused
+// multiply-add: the one-site kernel and 16-byte vectors round it once, straight
+// to FP16, narrower vectors to FP32 first, or once too with kRestOnce (for
+// lattices whose width was not chosen).
+template <int C, int NW, int kFField, bool kRestOnce = false>
 __device__ __forceinline__ void collide_sites(Lane<NW> (&d)[kQ], const Coll &cp, const Scale16 &sc, Range16 &rng,
                                               const float (&fxs)[NW * 4 / Codec<C>::kBytes],
                                               float (&mr)[NW * 4 / Codec<C>::kBytes],
@@ -1313,7 +1329,26 @@ __device__ __forceinline__ void collide_sites(Lane<NW> (&d)[kQ], const Coll &cp,
             collide(g0, cp, mr[2 * j], mu[2 * j], mv[2 * j], mw[2 * j]);
             collide(g1, cp, mr[2 * j + 1], mu[2 * j + 1], mv[2 * j + 1], mw[2 * j + 1]);
 #pragma unroll
-            for (int i = 0; i < kQ; ++i) d[i].w[j] = enc2_at<C>(g0[i], g1[i], sc, i, rng);
+            for (int i = 0; i < kQ; ++i) {
+                if (kRestOnce && i == 0) {
+                    uint32_t lo = enc_at<C>(g0[i], sc, i, rng), hi = enc_at<C>(g1[i], sc, i, rng);
+                    asm volatile("" : "+v"(lo));  // two conversions, not one of a pair
+                    asm volatile("" : "+v"(hi));
+                    d[i].w[j] = lo | (hi << 16);
+                } else {
+                    d[i].w[j] = enc2_at<C>(g0[i], g1[i], sc, i, rng);
+                }
+            }
+            if constexpr (C == kS16 && NW > 1) {
+                // the packed words as they now stand (interleaved with the
+                // next pair's decoding the kernel spills: 212 -> 277 us a
+                // step at 256^3)
+#pragma unroll
+                for (int i = 0; i < kQ; ++i) {
+#pragma unroll
+                    for (int k = 0; k < NW; ++k) asm volatile("" : "+v"(d[i].w[k]));
+                }
+            }
         }
     }
 }
@@ -1344,7 +1379,8 @@ __device__ __forceinline__ void s16_flag(const StepArgs &a, const Range16 &r)
 // like solid sites and take no part in the totals.  kFField: the x-force of
 // each site is the uniform one plus a per-site field (a.fx_field).  kPullNT:
 // as in gather.
-template <int C, int NW, bool kSolids, bool kMacros, bool kPadded, int NC, bool kFField = false, bool kPullNT = false>
+template <int C, int NW, bool kSolids, bool kMacros, bool kPadded, int NC, bool kFField = false, bool kPullNT = false,
+          bool kRestOnce = false>
 __device__ __forceinline__ void tile_update(const StepArgs &a, const char *src, char *dst, int tile,
                                             double (&acc)[NC], EdgeLds &lds)
 {
@@ -1365,7 +1401,7 @@ __device__ __forceinline__ void tile_update(const StepArgs &a, const char *src, 
         load_masks<V>(reinterpret_cast<const uint32_t *>(a.fx_field) + g.s0, reinterpret_cast<uint32_t(&)[V]>(fxs));
     }
     constexpr int kOrder = kSolids == (kMacros && NW == 1) ? 2 : 1;
-    collide_sites<C, NW, kFField ? kOrder : 0>(d, cp, a.sc, rng, fxs, mr, mu, mv, mw);
+    collide_sites<C, NW, kFField ? kOrder : 0, kRestOnce>(d, cp, a.sc, rng, fxs, mr, mu, mv, mw);
 
     if (g.active) {
         // Solid (and padding) sites hold zero in both arrays: they are

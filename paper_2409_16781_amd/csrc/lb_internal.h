@@ -144,6 +144,7 @@ struct StepArgs {
     TotalsArgs prev[2];       // launch, whose partials it wrote, to the ring
     int prev_own;             // set at the launch (prev_own_group): that is the launch's first workgroup, which does nothing
                               // else (the grid is one larger than the tiles)
+    int rest_once;            // kF16, 4-byte vectors: round the rest population once (collide_sites)
     Scale16 sc;               // kS16 only
     unsigned int *ovf;        // kS16 only: two flag words; this step ORs into ovf[par] bit c when a code
     int par;                  // of weight class c leaves its range, and skips (ORing bit 3 into ovf[par])

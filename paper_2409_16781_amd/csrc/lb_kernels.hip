@@ -96,8 +96,9 @@ __global__ __launch_bounds__(64) void reduce_totals(TotalsList list, int nsteps)
 // first (prev_own: as the tail of a tile's workgroup the append, 1-2 us, lies
 // on the critical path of a launch that is one round of workgroups; 32^3 step
 // 8.7 -> 7.5 us), on large ones that of the first tile.
-template <int C, int NW, bool kSolids, bool kMacros, int NC, bool kFField = false, bool kPullNT = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(vec_waves<C, NW>()))) void step_vec(StepArgs a)
+template <int C, int NW, bool kSolids, bool kMacros, int NC, bool kFField = false, bool kPullNT = false,
+          bool kRestOnce = false>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(vec_waves<C, NW>(), most_waves<C, NW, kFField>()))) void step_vec(StepArgs a)
 {
     __shared__ EdgeLds lds;
     if (s16_skip<C>(a)) return;
@@ -113,8 +114,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(vec_wave
     for (int k = 0; k < NC; ++k) acc[k] = 0.0;
     const int ntiles = (a.nslots + kBlock - 1) / kBlock;
     if (b < ntiles)
-        tile_update<C, NW, kSolids, kMacros, false, NC, kFField, kPullNT>(a, src, dst, tile_of(b, ntiles, a.tile_order),
-                                                                          acc, lds);
+        tile_update<C, NW, kSolids, kMacros, false, NC, kFField, kPullNT, kRestOnce>(
+            a, src, dst, tile_of(b, ntiles, a.tile_order), acc, lds);
     store_block_totals<NC>(acc, a.partials + NC * (size_t)b);
     if (a.nprev > 0 && !a.prev_own && b == 0) append_prev_totals<NC>(a.nprev, a.prev);
 }
@@ -503,8 +504,16 @@ void *pull_nt_fn(int variant)
 // pull_nt: plain steps with solids on the vector-row kernels pull with
 // non-temporal loads (ignored elsewhere).  split: totals in two parts (FP32
 // without solids; ignored on the one-site kernel and with a force field).
-void *pick_step(int codec, int variant, bool solids, bool macros, bool ffield, bool pull_nt = false, bool split = false)
+void *pick_step(int codec, int variant, bool solids, bool macros, bool ffield, bool pull_nt = false, bool split = false,
+                bool rest_once = false)
 {
+    if (rest_once && codec == kF16 && variant == 3) {
+        if (solids)
+            return macros ? reinterpret_cast<void *>(&step_vec<kF16, 1, true, true, 4, false, false, true>)
+                          : reinterpret_cast<void *>(&step_vec<kF16, 1, true, false, 4, false, false, true>);
+        return macros ? reinterpret_cast<void *>(&step_vec<kF16, 1, false, true, 4, false, false, true>)
+                      : reinterpret_cast<void *>(&step_vec<kF16, 1, false, false, 4, false, false, true>);
+    }
     if (split && !ffield && variant != 0)
         return macros ? step_fn<kF32, false, true, 8>(variant) : step_fn<kF32, false, false, 8>(variant);
     if (pull_nt && solids && !macros && !ffield && variant != 0) {
@@ -591,7 +600,7 @@ int step_occupancy(int codec, int variant, bool solids, bool macros)
 hipError_t launch_step(int codec, int variant, bool solids, bool macros, const StepArgs &a, int grid, hipStream_t s)
 {
     void *fn = pick_step(codec, variant, solids, macros, a.fx_field != nullptr, a.pull_nt != 0,
-                         a.split.m1 != 0.0);
+                         a.split.m1 != 0.0, a.rest_once != 0);
     StepArgs arg = a;
     arg.prev_own = prev_own_group(a, grid);
     void *params[] = {&arg};
