@@ -436,23 +436,15 @@ int enqueue_one(lb_lattice *h, int from, float *rho, float *u, hipStream_t s, co
 }
 
 // Enqueue count >= 1 steps without macros from buf[from] on stream s (they
-// end in buf[run_end]).  On the vector-row kernels the steps form a run: a
-// launch writes its partials into one of two buffers in turn, a workgroup of
-// the next launch appends their totals, and one totals kernel closes the run.
-// The ring then holds the same values as with a totals kernel after every
-// step.
+// end in buf[run_end]).  The steps form a run: a launch writes its partials
+// into one of two buffers in turn, a workgroup of the next launch appends
+// their totals, and one totals kernel closes the run.  The ring then holds the
+// same values as with a totals kernel after every step.
 int enqueue_run(lb_lattice *h, int from, int count, hipStream_t s, const TotalsBufs &tb, const RunPath *path,
                 float *const *mom, float *rho, float *u, bool totals)
 {
     if ((h->inplace || h->variant == 0) && (path || mom || rho || !totals))
         return fail(LB_EINVAL, "explicit step buffers need the two-array row kernels");
-    if (h->variant == 0) {
-        for (int k = 0; k < count; ++k) {
-            int rc = enqueue_one(h, from ^ (k & 1), nullptr, nullptr, s, tb);
-            if (rc) return rc;
-        }
-        return LB_OK;
-    }
     // Each launch takes one step or, where that is faster, two; it writes its
     // steps' partials into one of the two buffers in turn, and a workgroup of
     // the next launch appends their totals.  An odd step goes first, so a run

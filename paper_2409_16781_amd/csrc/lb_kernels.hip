@@ -127,19 +127,24 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(vec_wave
 template <int C, bool kSolids, bool kMacros>
 __global__ __launch_bounds__(kBlock) void step_site(StepArgs a)
 {
+    constexpr int NC = 4;
     if (s16_skip<C>(a)) return;
+    int b = blockIdx.x;
+    if (a.prev_own && b-- == 0) {
+        append_prev_totals<NC>(a.nprev, a.prev);
+        return;
+    }
     const Coll &cp = a.coll;
     const uint32_t nx = (uint32_t)a.nx, ny = (uint32_t)a.ny, nz = (uint32_t)a.nz;
     const char *src = reinterpret_cast<const char *>(a.src);
     char *dst = reinterpret_cast<char *>(a.dst);
-    constexpr int NC = 4;
     double acc[NC];
 #pragma unroll
     for (int k = 0; k < NC; ++k) acc[k] = 0.0;
     const int ntiles = (a.nslots + kBlock - 1) / kBlock;
     Range16 rng;  // kS16: range test of the codes
 
-    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    for (int tile = b; tile < ntiles; tile += (int)gridDim.x - a.prev_own) {
         const int slot = tile * kBlock + (int)threadIdx.x;
         if (slot >= a.nslots) continue;
         const uint32_t s = (uint32_t)slot;
@@ -190,7 +195,8 @@ __global__ __launch_bounds__(kBlock) void step_site(StepArgs a)
         add_moments<NC>(m, px, py, pz, acc, a.split);
     }
     if constexpr (C == kS16) s16_flag(a, rng);
-    store_block_totals<NC>(acc, a.partials + NC * (size_t)blockIdx.x);
+    store_block_totals<NC>(acc, a.partials + NC * (size_t)b);
+    if (a.nprev > 0 && !a.prev_own && b == 0) append_prev_totals<NC>(a.nprev, a.prev);
 }
 
 // Solid sites get zero macros in the one-site kernel (it skips them).
