@@ -6,8 +6,9 @@ k = 2 pi / 512) plus seeded uniform +-1e-3 noise on every velocity component,
 tau = 0.55, no body force; populations stored as FP32, FP16, BF16 or scaled
 16-bit fixed point (shifted by the lattice weights), FP32 arithmetic, FP64
 conservation totals every step.
-A step is one launch of the fused update over all 134,217,728 sites with the
-inputs already resident in HBM.
+A step is one fused update of all 134,217,728 sites with the inputs already
+resident in HBM; the library takes two FP32 steps per launch, and the roofline
+record is that of the one-step kernel timed alone.
 
 Prints one JSON line: MLUPS of the FP32-storage path as ``value``, the
 16-bit-storage results beside it, each codec's error against stored FP64
