@@ -484,6 +484,11 @@ int enqueue_run(lb_lattice *h, int from, int count, hipStream_t s, const TotalsB
             a.partials = buf;
             a.nprev = nprev;
             std::copy(prev, prev + 2, a.prev);
+            if (totals && count == 1 && !h->inplace && h->variant != 0 && h->codec != kS16 && h->grid <= kFinishGroups) {
+                a.finish = 1;
+                a.prev[0] = totals_args(h, buf, h->grid, tb, cur);
+                totals = false;
+            }
             if (h->inplace)
                 HIP_OR_FAIL(launch_aa_step(h->codec, h->variant, h->solids, cur == 0, a, h->grid, s));
             else

@@ -885,6 +885,30 @@ __device__ __forceinline__ void append_prev_totals(int n, const TotalsArgs (&pre
     }
 }
 
+// The totals of this launch's own step: the last of its workgroups to store
+// partials sums them, in the order of reduce_totals.  Saves a lone step of a
+// small lattice the totals kernel and the gap before it (32x16x8, a step with
+// its fields: 10.2 -> 8.0 us a call); each workgroup's release fence makes
+// it slow for many (kFinishGroups).  Not for scaled storage, whose flag must
+// be complete first.
+template <int NC>
+__device__ __forceinline__ void finish_totals(const TotalsArgs &t)
+{
+    if (threadIdx.x >= 64) return;  // the first wave stored the partials
+    __threadfence();
+    unsigned int arrived = 0;
+    if (threadIdx.x == 0) arrived = atomicAdd(&t.ticket[0], 1u);
+    if (__builtin_amdgcn_readfirstlane(arrived) != (unsigned int)t.nparts - 1) return;
+    __threadfence();
+    double tot[NC];
+    wave_sum<NC>(t.partials, t.nparts, tot, true);
+    if (threadIdx.x != 0) return;
+    const unsigned long long step = __hip_atomic_load(t.step_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    store_ring<NC>(t, step, tot);
+    __hip_atomic_store(&t.ticket[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(t.step_counter, step + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ------------------------------------------------ step: vector-row kernel --
 // A lane owns V consecutive sites of one x-row (nx % V == 0) and moves one
 // 4-, 8- or 16-byte vector per population in each direction.  Lanes of a wave

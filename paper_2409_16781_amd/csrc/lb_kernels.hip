@@ -117,6 +117,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(vec_wave
         tile_update<C, NW, kSolids, kMacros, false, NC, kFField, kPullNT, kRestOnce>(
             a, src, dst, tile_of(b, ntiles, a.tile_order), acc, lds);
     store_block_totals<NC>(acc, a.partials + NC * (size_t)b);
+    if constexpr (C != kS16)
+        if (a.finish) finish_totals<NC>(a.prev[0]);
     if (a.nprev > 0 && !a.prev_own && b == 0) append_prev_totals<NC>(a.nprev, a.prev);
 }
 
