@@ -343,7 +343,7 @@ MarchShape march_shape(int nx, int ny, int nz, int cus)
             const int chunk = (ny + chunks - 1) / chunks;
             if ((ny + chunk - 1) / chunk != chunks) continue;
             const int64_t tiles = (int64_t)best.nxt * nzt * chunks;
-            if (tiles > (1 << 30)) break;
+            if (tiles > 64 * (int64_t)cus && chunks > 1) break;  // shorter chunks only add halos
             const double rounds = (double)((tiles + cus - 1) / cus);
             const double us = (tiles % cus == 0 ? 9.5 : 3.5) + rounds * (chunk + 2) * (0.07 + 0.36 * (rows + 3)) * sectors;
             if (us < best_us) {
