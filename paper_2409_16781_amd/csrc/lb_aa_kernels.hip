@@ -131,7 +131,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(push_wav
     __shared__ EdgeLds lds;
     __shared__ uint32_t dead_row_last[kBlock], dead_row_first[kBlock], dead_wave_last[4], dead_wave_first[4];
     int b = blockIdx.x;
-    if (a.prev_own && b-- == 0) {
+    // split totals: behind the tile's work, as in step_vec
+    if constexpr (NC == 8) {
+        b -= a.prev_own;
+    } else if (a.prev_own && b-- == 0) {
         append_prev_totals<NC>(a.nprev, a.prev);
         return;
     }
@@ -144,7 +147,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(push_wav
     const int wave = threadIdx.x >> 6;
     const int rit = (int)threadIdx.x >> a.lg_row_lanes;
     const int ntiles = (a.nslots + kBlock - 1) / kBlock;
-    if (b < ntiles) {  // one workgroup per tile
+    if ((NC != 8 || b >= 0) && b < ntiles) {  // one workgroup per tile
         const TileGeom g = tile_geom<V, false>(a, tile_of(b, ntiles, a.tile_order));
         Lane<NW> d[kQ];
         const uint32_t dead = gather<C, NW, kSolids, false, true>(a, F, g, d, lds);
@@ -251,8 +254,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(push_wav
         }
         (void)nz;
     }
-    store_block_totals<NC>(acc, a.partials + NC * (size_t)b);
-    if (a.nprev > 0 && !a.prev_own && b == 0) append_prev_totals<NC>(a.nprev, a.prev);
+    if (NC != 8 || b >= 0) store_block_totals<NC>(acc, a.partials + NC * (size_t)b);
+    if (a.nprev > 0 && (NC == 8 ? blockIdx.x == 0 : !a.prev_own && b == 0)) append_prev_totals<NC>(a.nprev, a.prev);
 }
 
 }  // namespace

@@ -289,6 +289,8 @@ TotalsArgs totals_args(const lb_lattice *h, const double *partials, int nparts, 
     TotalsArgs t{};
     t.ovf = h->codec == kS16 ? h->ovf + par : nullptr;
     t.nc = total_parts_of(h);
+    t.e1 = h->split.e1;
+    t.e2 = h->split.e2;
     t.partials = partials;
     t.nparts = nparts;
     t.gpartials = tb.gpartials;
@@ -813,7 +815,7 @@ int create_impl(lb_lattice **out, int nx, int ny, int nz, double tau, const uint
     const long two = env_long("LB_TWO_STEP", 1);
     if (storage == LB_F32 && !h->solids && h->variant != 0) {
         h->march = march_shape(nx, ny, nz, h->cus);
-        if (h->march.use || two != 1) h->split = total_split(n);
+        if (h->march.use || two != 1) h->split = total_split(std::max(4 * kBlock, 64 * h->march.chunk));
         h->march.use = !inplace && (two == 2 || (two == 1 && h->march.use));
     }
 
@@ -1472,16 +1474,11 @@ int lb_tune(lb_lattice *h, int reps)
             const size_t nc = total_parts_of(h);
             a.partials = h->partials + (size_t)(k & 1) * nc * c.grid;
             if (k > 0) {
-                TotalsArgs t{};
-                t.nc = (int)nc;
-                t.partials = h->partials + (size_t)((k - 1) & 1) * nc * c.grid;
-                t.nparts = c.grid;
-                t.gpartials = h->gpartials;
-                t.ring = tring;
-                t.step_counter = tctr;
-                t.n_fluid = h->n_fluid;
                 a.nprev = 1;
-                a.prev[0] = t;
+                a.prev[0] = totals_args(h, h->partials + (size_t)((k - 1) & 1) * nc * c.grid, c.grid, own_bufs(h), 0);
+                a.prev[0].ovf = nullptr;
+                a.prev[0].ring = tring;
+                a.prev[0].step_counter = tctr;
             }
             if (launch_step(h->codec, c.variant, h->solids, false, a, c.grid, h->stream) != hipSuccess)
                 rc = fail(LB_EHIP, "step kernel launch");

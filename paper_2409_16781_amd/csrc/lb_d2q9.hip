@@ -41,6 +41,7 @@ struct lb2d_lattice {
     int variant = 1, vsites = 4, grid = 1;
     March2Shape march[kMaxSteps + 1] = {};  // of launches of 2 and 4 steps
     int most = 1;                           // most steps of one launch
+    TotalSplit split = {};
     size_t parts = 1;                       // partials of one of a run's two buffers
     long long steps = 0;
 };
@@ -88,7 +89,7 @@ Step2Args step2_args(const lb2d_lattice *h, int from)
     }
     a.nbmask = h->nbmask;
     a.chunkdirty = h->chunkdirty;
-    a.split = total_split(h->n);
+    a.split = h->split;
     return a;
 }
 
@@ -97,6 +98,8 @@ TotalsArgs totals2(const lb2d_lattice *h, const double *partials, int nparts)
 {
     TotalsArgs t{};
     t.nc = 8;
+    t.e1 = h->split.e1;
+    t.e2 = h->split.e2;
     t.partials = partials;
     t.nparts = nparts;
     t.gpartials = h->gpartials;
@@ -242,6 +245,8 @@ lb2d_lattice *lb2d_create(int nx, int ny, double tau, const uint8_t *flags, doub
             h->most = k;
         }
     }
+    // (the same for every number of steps a launch)
+    h->split = total_split(std::max({4 * kBlock, h->march[2].group, h->march[4].group}));
     for (int k = 2; k <= h->most; k *= 2) h->parts = std::max(h->parts, (size_t)k * h->march[k].nitems);
 
     auto bail = [&](int code, const char *what, hipError_t e) -> lb2d_lattice * {

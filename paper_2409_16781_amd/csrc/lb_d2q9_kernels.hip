@@ -629,11 +629,13 @@ March2Shape march2_shape(int variant, int steps, int nx, int ny, int cus)
     March2Shape best{};
     best.us = 1e300;
     const int nstrips = (nv + 64 - 2 * H - 1) / (64 - 2 * H);
-    for (int chunks = 1; chunks <= ny; ++chunks) {
+    best.group = (64 - 2 * H) * V;
+    const int fewest = (ny + kMarchChunk - 1) / kMarchChunk;
+    for (int chunks = fewest; chunks <= ny; ++chunks) {
         const int chunk = (ny + chunks - 1) / chunks;
         if ((ny + chunk - 1) / chunk != chunks) continue;
         const int64_t waves = (int64_t)nstrips * chunks;
-        if (waves > 64 * (int64_t)simds && chunks > 1) break;
+        if (waves > 64 * (int64_t)simds && chunks > fewest) break;
         const double rounds = (double)((waves + 2 * simds - 1) / (2 * simds));
         const double row = (V == 2 ? 1.0 : 0.62) * (waves <= simds ? (steps == 4 ? 2.7 : 1.56) : (steps == 4 ? 3.9 : 2.6));
         const double us = (steps == 4 ? 9.0 : 6.0) + rounds * (chunk + 2 * steps) * row;
@@ -644,6 +646,7 @@ March2Shape march2_shape(int variant, int steps, int nx, int ny, int cus)
             best.nitems = (int)waves;
         }
     }
+    best.group *= best.chunk;
     return best;
 }
 

@@ -612,13 +612,16 @@ __device__ __forceinline__ void moments_of_totals_by_class(const int (&t)[kQ], i
 // same bits.  FP32 values have no common quantum: there each site's moment m
 // is split into two multiples of fixed quanta,
 //   hi = (m + M1) - M1,   lo = ((m - hi) + M2) - M2,
-// chosen for the lattice's size (total_split) so that sums of hi and sums of
-// lo are both exact.  hi + lo differs from m by at most half of the second
-// quantum (2^-52 at 512^3, less on smaller lattices), the same for a site
-// whichever kernel computes it, so the totals of a step do not depend on how
-// the sites were dealt to lanes, workgroups or launches: a step taken as half
-// of a two-step launch gives the bits of one taken alone.  (24 more additions
-// a site: 0 to 2% of an FP32 step, 3% where it works from the caches.)
+// chosen for the sites that one workgroup sums (total_split) so that its sums
+// of hi and of lo are both exact; the workgroups' sums are added as integers
+// (sum_split).  The totals of a step then do not depend on how the sites
+// were dealt to lanes, workgroups or launches: a step taken as half of a
+// two-step launch gives the bits of one taken alone.  hi + lo differs from m by
+// at most half of the second quantum, 2^(2 lg W - 106) for workgroups of W
+// sites: 2^-86 up to 1024 sites, 2^-80 at 512^3, 2^-74 at most.  That is below
+// the FP64 rounding of m itself for |m| > 1e-10, 7e-9 and 5e-7.  (24 more
+// additions a site: 0 to 2% of an FP32 step, 3% where it works from the caches;
+// a caller who takes one step at a time pays them too.)
 // Only lattices that take two-step launches (and in-place ones of the same
 // extents) split: NC = 8 doubles of totals instead of 4, a template argument
 // of the vector-row steps.
@@ -643,9 +646,9 @@ __device__ __forceinline__ void add_moments(double m, double px, double py, doub
 // FP64 totals of the values a lane stores: every stored element is converted
 // to double and combined into {mass deviation, momentum} in FP64 and in a
 // fixed order (dead elements hold zero and add nothing).  The stored values
-// are exact in double, so a lane's totals carry only FP64 rounding (~1e-16
-// relative).  NC = 4: a lane's sites are summed per direction first (fewer
-// additions); NC = 8: each site's moments are split and summed by parts.
+// are exact in double.  NC = 4: a lane's sites are summed per direction first
+// (fewer additions), and its totals carry only FP64 rounding (~1e-16
+// relative); NC = 8: each site's moments are split and summed by parts.
 template <int C, int NW, int NC>
 __device__ __forceinline__ void add_lane_totals(const Lane<NW> (&d)[kQ], double (&acc)[NC], const Scale16 &sc,
                                                 const TotalSplit &sp)
@@ -829,17 +832,145 @@ __device__ __forceinline__ void wave_sum(const double *v, int count, double (&ou
     }
 }
 
-// {mass, momentum} of step number `step` from its summed parts, into the ring
-// (one thread).
-template <int NC>
-__device__ __forceinline__ void store_ring(const TotalsArgs &t, unsigned long long step, const double (&tot)[NC])
+typedef __int128 i128;
+
+__device__ __forceinline__ i128 shfl_xor128(i128 v, int off)
+{
+    const unsigned long long lo = __shfl_xor((unsigned long long)v, off, 64);
+    const unsigned long long hi = __shfl_xor((unsigned long long)((unsigned __int128)v >> 64), off, 64);
+    return (i128)((unsigned __int128)hi << 64 | lo);
+}
+
+// v 2^e, rounded to nearest even.
+__device__ __forceinline__ double scaled_to_double(i128 v, int e)
+{
+    const bool neg = v < 0;
+    const unsigned __int128 u = neg ? -(unsigned __int128)v : (unsigned __int128)v;
+    unsigned long long top = (unsigned long long)(u >> 64);
+    int exp = e;
+    if (top != 0) {
+        const int lz = __builtin_clzll(top);
+        const unsigned __int128 w = u << lz;  // 64 leading bits, the others as one sticky bit
+        top = (unsigned long long)(w >> 64) | ((unsigned long long)w != 0 ? 1ull : 0ull);
+        exp += 64 - lz;
+    } else {
+        top = (unsigned long long)u;
+    }
+    const double d = __builtin_ldexp((double)top, exp);
+    return neg ? -d : d;
+}
+
+// ------------------------------------------------------------ split totals --
+// The workgroups' sums of first and second parts are added as integer
+// multiples of the second quantum 2^e2, component t % 4 by thread t.  An
+// integer sum has no order, and it is exact: a workgroup's first parts are
+// below 2^53 of their quanta, 2^(54 - lg sites) second quanta each, so with
+// 2^10 sites or more a workgroup and 2^31 in all a sum stays below 2^122.
+// Partials beyond that (moments over 4 a site on average, or not finite) are
+// added in FP64 beside it.  (The code runs once a launch, from instructions
+// that no other workgroup needs, so its time goes with its length: with all
+// four components in each thread a 256^2 D2Q9 step, four to a launch, took 10.5
+// us instead of 5.0, and the registers left the 4-byte steps of an FP32 lattice
+// four waves a SIMD instead of seven.)
+struct SplitSum {
+    i128 x;    // multiple of 2^e2
+    double d;  // partials out of its range
+};
+
+// A thread's share of partials [first, first + count), every stride-th, four
+// loaded together.  coherent: they were written earlier in this launch.
+__device__ __forceinline__ SplitSum sum_split(const TotalsArgs &t, int first, int count, int stride, bool coherent)
+{
+    const double lim1 = __builtin_ldexp(1.0, t.e1 + 53), lim2 = __builtin_ldexp(1.0, t.e2 + 53);
+    const double *p = t.partials + 8 * (size_t)first + (threadIdx.x & 3);
+    i128 hi = 0, lo = 0;
+    double wild = 0.0;
+#pragma unroll 1
+    for (int base = threadIdx.x >> 2; base < count; base += 4 * stride) {
+        double h[4], l[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int b = base + q * stride;
+            h[q] = l[q] = 0.0;
+            if (b < count) {
+                const double *at = p + 8 * (size_t)b;
+                h[q] = coherent ? __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : at[0];
+                l[q] = coherent ? __hip_atomic_load(at + 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : at[4];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool in = __builtin_fabs(h[q]) <= lim1 && __builtin_fabs(l[q]) <= lim2;
+            hi += (long long)__builtin_ldexp(in ? h[q] : 0.0, -t.e1);
+            lo += (long long)__builtin_ldexp(in ? l[q] : 0.0, -t.e2);
+            wild += in ? 0.0 : h[q] + l[q];
+        }
+    }
+    return SplitSum{(hi << (t.e1 - t.e2)) + lo, wild};
+}
+
+// The sums over a wave of the components: in each lane that of lane % 4.
+__device__ __forceinline__ SplitSum wave_split(SplitSum s)
+{
+#pragma unroll
+    for (int off = 4; off < 64; off *= 2) {
+        s.x += shfl_xor128(s.x, off);
+        s.d += __shfl_xor(s.d, off, 64);
+    }
+    return s;
+}
+
+template <int M, int WAVES>
+struct SplitLds {
+    unsigned long long sums[WAVES][M][4][2];
+    double wild[WAVES][M][4];
+};
+
+// n sums (the k-th of each thread from sum(k)) over a workgroup: valid in
+// threads 4 k + component.
+template <int M, int WAVES, class F>
+__device__ __forceinline__ SplitSum block_split(int n, SplitLds<M, WAVES> &lds, F &&sum)
+{
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll 1
+    for (int k = 0; k < n; ++k) {
+        const SplitSum s = wave_split(sum(k));
+        if (lane < 4) {
+            lds.sums[w][k][lane][0] = (unsigned long long)s.x;
+            lds.sums[w][k][lane][1] = (unsigned long long)((unsigned __int128)s.x >> 64);
+            lds.wild[w][k][lane] = s.d;
+        }
+    }
+    __syncthreads();
+    SplitSum s{0, 0.0};
+    if ((int)threadIdx.x < 4 * n) {
+        const int k = threadIdx.x >> 2, c = threadIdx.x & 3;
+#pragma unroll 1
+        for (int i = 0; i < WAVES; ++i) {
+            s.x += (i128)((unsigned __int128)lds.sums[i][k][c][1] << 64 | lds.sums[i][k][c][0]);
+            s.d += lds.wild[i][k][c];
+        }
+    }
+    return s;
+}
+
+// A component of the totals of step number `step` into the ring.
+__device__ __forceinline__ void store_split(const TotalsArgs &t, unsigned long long step, const SplitSum &s)
+{
+    const double v = scaled_to_double(s.x, t.e2) + s.d;
+    const int c = threadIdx.x & 3;
+    t.ring[4 * (step % kRingCap) + c] = c == 0 ? t.n_fluid + v : v;
+}
+
+// {mass, momentum} of step number `step` from its sums, into the ring (one
+// thread).
+__device__ __forceinline__ void store_ring(const TotalsArgs &t, unsigned long long step, const double (&tot)[4])
 {
     double *r = t.ring + 4 * (step % kRingCap);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const double v = NC == 8 ? tot[k] + tot[NC - 4 + k] : tot[k];
-        r[k] = k == 0 ? t.n_fluid + v : v;
-    }
+    r[0] = t.n_fluid + tot[0];
+    r[1] = tot[1];
+    r[2] = tot[2];
+    r[3] = tot[3];
 }
 
 // The totals of one step from its workgroup partials t.partials, summed by a
@@ -848,40 +979,62 @@ __device__ __forceinline__ void store_ring(const TotalsArgs &t, unsigned long lo
 // is bitwise the same) and appended to the ring.  The waves take chunks in
 // turn; the first wave sums the chunk sums.  The partials were written by an
 // earlier launch, so no fence is needed before reading them.
-template <int NC>
 __device__ __forceinline__ void append_step_totals(const TotalsArgs &t)
 {
     const int nchunks = (t.nparts + kRedChunk - 1) / kRedChunk;
     for (int c = (int)threadIdx.x >> 6; c < nchunks; c += (int)blockDim.x >> 6) {
-        double gs[NC];
-        wave_sum<NC>(t.partials + NC * (size_t)c * kRedChunk, min(kRedChunk, t.nparts - c * kRedChunk), gs);
+        double gs[4];
+        wave_sum<4>(t.partials + 4 * (size_t)c * kRedChunk, min(kRedChunk, t.nparts - c * kRedChunk), gs);
         if ((threadIdx.x & 63) == 0) {
 #pragma unroll
-            for (int k = 0; k < NC; ++k)
-                __hip_atomic_store(&t.gpartials[NC * c + k], gs[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int k = 0; k < 4; ++k)
+                __hip_atomic_store(&t.gpartials[4 * c + k], gs[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __syncthreads();  // every wave's chunk sums are stored
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     if (threadIdx.x < 64) {
-        double tot[NC];
-        wave_sum<NC>(t.gpartials, nchunks, tot, true);
+        double tot[4];
+        wave_sum<4>(t.gpartials, nchunks, tot, true);
         if (threadIdx.x == 0) {
             const unsigned long long step = __hip_atomic_load(t.step_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            store_ring<NC>(t, step, tot);
+            store_ring(t, step, tot);
             __hip_atomic_store(t.step_counter, step + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }
 
-// The totals of the n (1..M) steps of the previous launch, in order.
+// The totals of the n (1..M) steps of the previous launch, in order: split
+// totals in WAVES waves ...
+template <int M, int WAVES>
+__device__ __forceinline__ void append_split_totals(int n, const TotalsArgs (&prev)[M], SplitLds<M, WAVES> &lds)
+{
+    const SplitSum s = block_split(n, lds, [&](int k) __attribute__((always_inline)) {
+        return sum_split(prev[k], 0, prev[k].nparts, 16 * WAVES, false);
+    });
+    if (threadIdx.x < 64) {
+        const unsigned long long step = __hip_atomic_load(prev[0].step_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((int)threadIdx.x < 4 * n) store_split(prev[0], step + (threadIdx.x >> 2), s);
+        if (threadIdx.x == 0) __hip_atomic_store(prev[0].step_counter, step + n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // no load in flight: a kernel whose tile comes behind this has none of its
+    // registers to wait for
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+}
+
+// ... and either kind in a workgroup of kBlock threads.
 template <int NC, int M>
 __device__ __forceinline__ void append_prev_totals(int n, const TotalsArgs (&prev)[M])
 {
-    for (int k = 0; k < n; ++k) {
-        if (k > 0) __syncthreads();  // the chunk sums are rewritten
-        append_step_totals<NC>(prev[k]);
+    if constexpr (NC == 8) {
+        __shared__ SplitLds<M, kBlock / 64> lds;
+        append_split_totals(n, prev, lds);
+    } else {
+        for (int k = 0; k < n; ++k) {
+            if (k > 0) __syncthreads();  // the chunk sums are rewritten
+            append_step_totals(prev[k]);
+        }
     }
 }
 
@@ -900,11 +1053,16 @@ __device__ __forceinline__ void finish_totals(const TotalsArgs &t)
     if (threadIdx.x == 0) arrived = atomicAdd(&t.ticket[0], 1u);
     if (__builtin_amdgcn_readfirstlane(arrived) != (unsigned int)t.nparts - 1) return;
     __threadfence();
-    double tot[NC];
-    wave_sum<NC>(t.partials, t.nparts, tot, true);
-    if (threadIdx.x != 0) return;
     const unsigned long long step = __hip_atomic_load(t.step_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    store_ring<NC>(t, step, tot);
+    if constexpr (NC == 8) {
+        const SplitSum s = wave_split(sum_split(t, 0, t.nparts, 16, true));
+        if (threadIdx.x < 4) store_split(t, step, s);
+    } else {
+        double tot[NC];
+        wave_sum<NC>(t.partials, t.nparts, tot, true);
+        if (threadIdx.x == 0) store_ring(t, step, tot);
+    }
+    if (threadIdx.x != 0) return;
     __hip_atomic_store(&t.ticket[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(t.step_counter, step + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -1140,7 +1298,12 @@ __device__ __forceinline__ uint32_t gather(const StepArgs &a, const char *src, c
         rb[i] = a.lay.row_base(zs * ny + ys) + (uint64_t)(kSwap ? OPP[i] : i) * a.lay.seg;
     }
 #pragma unroll
-    for (int i = 0; i < kQ; ++i) d[i] = ldv<NW, !kSolids || kPullNT>(src + (rb[i] + x0) * K::kBytes);
+    for (int i = 0; i < kQ; ++i) {
+        d[i] = ldv<NW, !kSolids || kPullNT>(src + (rb[i] + x0) * K::kBytes);
+        // in place, each load behind its own address instead of all behind all
+        // addresses: 256^3 gather-and-push step 417 -> 412 us
+        if constexpr (kSwap && !kSolids && C == kF32) __builtin_amdgcn_sched_barrier(0);
+    }
     // Waves with a dead site or a bounce-back issue their neighbour masks
     // right behind the pulls (one round trip for both); the others read no
     // mask at all.

@@ -24,12 +24,13 @@ struct Scale16 {
 };
 
 // Splitting constants of FP32 totals (add_moments): 1.5 * 2^52 times the two
-// quanta of the lattice.
+// quanta 2^e1 and 2^e2.
 struct TotalSplit {
     double m1, m2;
+    int e1, e2;
 };
 
-TotalSplit total_split(uint64_t sites);
+TotalSplit total_split(uint64_t group);
 
 struct Shift16 {
     int sh[3];  // per weight class: codes divided by 2^sh (widening the range)
@@ -104,6 +105,7 @@ struct TotalsArgs {
     const double *partials;   // nc doubles per step workgroup
     int nparts;               // step workgroups
     int nc;                   // 4, or 8 where the moments are summed in two parts (FP32 lattices)
+    int e1, e2;               // of the two parts (TotalSplit)
     double *gpartials;        // nc doubles per reduce workgroup, for each step of a launch
     unsigned int *ticket;     // kTickets arrival counters, 0 between launches
     double *ring;             // kRingCap x 4 doubles
@@ -167,6 +169,9 @@ inline int prev_own_group(const StepArgs &a, int grid) { return a.nprev > 0 && g
 // columns (x), rows planes (z) and chunk rows (y); the last ones of each axis
 // may be shorter.
 constexpr int kMarchRows = 13;  // most planes of a tile
+// Most rows of a chunk, here and in march2d: more would save nothing (two or
+// eight halo rows a chunk) and cost the totals bits (total_split).
+constexpr int kMarchChunk = 512;
 
 struct MarchShape {
     int nxt, nyt, nzt;        // tiles along x, y and z
@@ -277,6 +282,7 @@ struct March2Args {
 
 struct March2Shape {
     int nstrips, chunk, nitems;
+    int group;                // sites of one item
     double us;                // estimated time of a launch
 };
 

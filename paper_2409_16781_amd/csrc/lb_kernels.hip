@@ -43,14 +43,16 @@ struct TotalsList {
 };
 
 // The totals of the steps of the last launch of a run (step blockIdx.y).
-// Workgroup g, one wave, sums partials [g * kRedChunk, (g + 1) * kRedChunk)
-// into gpartials[g]; a step's last workgroup to finish sums the gpartials in
-// order and stores {mass, momentum} of the step in the ring; the last of
-// those advances the step counter.  (A wave's registers and shuffles instead
-// of a workgroup's LDS tree and its sixteen barriers: the same additions,
-// 5.2 -> 3.4 us for the few partials of a small lattice.)
+// Workgroup g, one wave (NC = 8: four), sums partials [g * kRedChunk,
+// (g + 1) * kRedChunk) into gpartials[g]; a step's last workgroup to finish sums
+// the gpartials in order and stores {mass, momentum} of the step in the ring;
+// the last of those advances the step counter.  (A wave's registers and
+// shuffles instead of a workgroup's LDS tree and its sixteen barriers: the same
+// additions, 5.2 -> 3.4 us for the few partials of a small lattice.)
+constexpr int red_threads(int nc) { return nc == 8 ? 256 : 64; }
+
 template <int NC>
-__global__ __launch_bounds__(64) void reduce_totals(TotalsList list, int nsteps)
+__global__ __launch_bounds__(red_threads(NC)) void reduce_totals(TotalsList list, int nsteps)
 {
     const int s = blockIdx.y;
     const TotalsArgs &a = list.t[s];
@@ -60,25 +62,69 @@ __global__ __launch_bounds__(64) void reduce_totals(TotalsList list, int nsteps)
     if ((int)blockIdx.x >= nchunks) return;
     const int first = blockIdx.x * kRedChunk;
     const int count = min(kRedChunk, a.nparts - first);
-    double gs[NC];
-    wave_sum<NC>(a.partials + NC * (size_t)first, count, gs);
-    if (nchunks > 1) {
-        double *gp = a.gpartials + NC * (size_t)(s * gridDim.x);
-        unsigned int prev = 0;
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int k = 0; k < NC; ++k)
-                __hip_atomic_store(&gp[NC * blockIdx.x + k], gs[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __threadfence();
-            prev = atomicAdd(&a.ticket[s], 1u);
+    double *gp = a.gpartials + NC * (size_t)(s * gridDim.x);
+    // whether this is the step's last workgroup to store its chunk's sums
+    auto last_one = [&]() __attribute__((always_inline)) {
+        __shared__ unsigned int arrived;
+        if (threadIdx.x < 64) __threadfence();  // the first wave stored the sums
+        if (threadIdx.x == 0) arrived = atomicAdd(&a.ticket[s], 1u);
+        __syncthreads();
+        const bool is_last = arrived == (unsigned int)nchunks - 1;
+        if (is_last) __threadfence();
+        return is_last;
+    };
+    [[maybe_unused]] __shared__ SplitLds<1, red_threads(NC) / 64> lds;
+    [[maybe_unused]] double gs[4];
+    [[maybe_unused]] SplitSum x;
+    if constexpr (NC == 8) {
+        x = block_split(1, lds, [&](int) __attribute__((always_inline)) {
+            return sum_split(a, first, count, red_threads(NC) / 4, false);
+        });
+        if (nchunks > 1) {
+            // a chunk with partials out of range: its FP64 sum, and a high word
+            // that no sum reaches
+            constexpr unsigned long long kMark = 1ull << 63;
+            unsigned long long *w = reinterpret_cast<unsigned long long *>(gp);
+            if (threadIdx.x < 4) {
+                unsigned long long *to = w + 8 * (size_t)blockIdx.x + 2 * threadIdx.x;
+                unsigned long long lo = (unsigned long long)x.x, hi = (unsigned long long)((unsigned __int128)x.x >> 64);
+                if (x.d != 0.0) {
+                    lo = __builtin_bit_cast(unsigned long long, scaled_to_double(x.x, a.e2) + x.d);
+                    hi = kMark;
+                }
+                __hip_atomic_store(to, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(to + 1, hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (!last_one()) return;
+            SplitSum y{0, 0.0};
+            for (int c = threadIdx.x >> 2; c < nchunks; c += red_threads(NC) / 4) {
+                const unsigned long long *from = w + 8 * (size_t)c + 2 * (threadIdx.x & 3);
+                const unsigned long long lo = __hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const unsigned long long hi = __hip_atomic_load(from + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (hi == kMark)
+                    y.d += __builtin_bit_cast(double, lo);
+                else
+                    y.x += (i128)((unsigned __int128)hi << 64 | lo);
+            }
+            x = block_split(1, lds, [&](int) __attribute__((always_inline)) { return y; });
         }
-        if (__builtin_amdgcn_readfirstlane(prev) != (unsigned int)nchunks - 1) return;
-        __threadfence();
-        wave_sum<NC>(gp, nchunks, gs, true);
+    } else {
+        wave_sum<NC>(a.partials + NC * (size_t)first, count, gs);
+        if (nchunks > 1) {
+            if (threadIdx.x == 0) {
+#pragma unroll
+                for (int k = 0; k < NC; ++k)
+                    __hip_atomic_store(&gp[NC * blockIdx.x + k], gs[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (!last_one()) return;
+            wave_sum<NC>(gp, nchunks, gs, true);
+        }
     }
-    if (threadIdx.x != 0) return;
     const unsigned long long step = __hip_atomic_load(a.step_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    store_ring<NC>(a, step + s, gs);
+    if constexpr (NC == 8)
+        if (threadIdx.x < 4) store_split(a, step + s, x);
+    if (threadIdx.x != 0) return;
+    if constexpr (NC != 8) store_ring(a, step + s, gs);
     __hip_atomic_store(&a.ticket[s], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (nsteps > 1) {
         // the step counter was read above before another step can advance it
@@ -103,23 +149,30 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(vec_wave
     __shared__ EdgeLds lds;
     if (s16_skip<C>(a)) return;
     int b = blockIdx.x;
-    if (a.prev_own && b-- == 0) {
+    // Split totals are appended behind the tile's work: before it, the compiler
+    // has every wave wait for its stores ahead of the totals (512^3 step 3165 ->
+    // 3340 us).
+    if constexpr (NC == 8) {
+        b -= a.prev_own;
+    } else if (a.prev_own && b-- == 0) {
         append_prev_totals<NC>(a.nprev, a.prev);
         return;
     }
-    const char *src = reinterpret_cast<const char *>(a.src);
-    char *dst = reinterpret_cast<char *>(a.dst);
-    double acc[NC];
+    if (NC != 8 || b >= 0) {
+        const char *src = reinterpret_cast<const char *>(a.src);
+        char *dst = reinterpret_cast<char *>(a.dst);
+        double acc[NC];
 #pragma unroll
-    for (int k = 0; k < NC; ++k) acc[k] = 0.0;
-    const int ntiles = (a.nslots + kBlock - 1) / kBlock;
-    if (b < ntiles)
-        tile_update<C, NW, kSolids, kMacros, false, NC, kFField, kPullNT, kRestOnce>(
-            a, src, dst, tile_of(b, ntiles, a.tile_order), acc, lds);
-    store_block_totals<NC>(acc, a.partials + NC * (size_t)b);
-    if constexpr (C != kS16)
-        if (a.finish) finish_totals<NC>(a.prev[0]);
-    if (a.nprev > 0 && !a.prev_own && b == 0) append_prev_totals<NC>(a.nprev, a.prev);
+        for (int k = 0; k < NC; ++k) acc[k] = 0.0;
+        const int ntiles = (a.nslots + kBlock - 1) / kBlock;
+        if (b < ntiles)
+            tile_update<C, NW, kSolids, kMacros, false, NC, kFField, kPullNT, kRestOnce>(
+                a, src, dst, tile_of(b, ntiles, a.tile_order), acc, lds);
+        store_block_totals<NC>(acc, a.partials + NC * (size_t)b);
+        if constexpr (C != kS16)
+            if (a.finish) finish_totals<NC>(a.prev[0]);
+    }
+    if (a.nprev > 0 && (NC == 8 ? blockIdx.x == 0 : !a.prev_own && b == 0)) append_prev_totals<NC>(a.nprev, a.prev);
 }
 
 // ---------------------------------------------- step: one site per thread --
@@ -576,17 +629,17 @@ Coll make_coll(float omega, float fx, float fy, float fz)
     return p;
 }
 
-// Quanta of the two parts of FP32 totals on a lattice of n sites: the sums
-// of up to n first parts of magnitude at most 4, and of n second parts of at
-// most half the first quantum, stay below 2^53 of their quanta (exact).
-// Larger moments (a blown-up state) only lose the independence of the order,
-// not accuracy.
-TotalSplit total_split(uint64_t n)
+// Quanta of the two parts of FP32 totals where a workgroup sums up to group
+// sites: the sums of that many first parts of magnitude at most 4, and of
+// second parts of at most half the first quantum, stay below 2^53 of their
+// quanta (exact).  Larger moments (a blown-up state) only lose the
+// independence of the order, not accuracy.
+TotalSplit total_split(uint64_t group)
 {
-    int lg = 0;
-    while ((1ull << lg) < n) ++lg;
+    int lg = 10;
+    while ((1ull << lg) < group) ++lg;
     const int e1 = lg + 2 - 53, e2 = (e1 - 1) + lg - 53;
-    return TotalSplit{std::ldexp(1.5, 52 + e1), std::ldexp(1.5, 52 + e2)};
+    return TotalSplit{std::ldexp(1.5, 52 + e1), std::ldexp(1.5, 52 + e2), e1, e2};
 }
 
 int sites_per_thread(int codec, int variant)
@@ -650,9 +703,9 @@ hipError_t launch_totals(const TotalsArgs *a, int nsteps, hipStream_t s)
     TotalsList list{};
     std::copy(a, a + nsteps, list.t);
     if (a[0].nc == 8)
-        reduce_totals<8><<<dim3(g, nsteps), 64, 0, s>>>(list, nsteps);
+        reduce_totals<8><<<dim3(g, nsteps), red_threads(8), 0, s>>>(list, nsteps);
     else
-        reduce_totals<4><<<dim3(g, nsteps), 64, 0, s>>>(list, nsteps);
+        reduce_totals<4><<<dim3(g, nsteps), red_threads(4), 0, s>>>(list, nsteps);
     return hipGetLastError();
 }
 

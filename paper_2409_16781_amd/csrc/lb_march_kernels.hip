@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kMThreads) void march2(MarchArgs a)
     __shared__ Exchange ex;
     int t = blockIdx.x;
     if (a.nprev > 0 && t-- == 0) {
-        append_prev_totals<8>(a.nprev, a.prev);
+        append_split_totals(a.nprev, a.prev, reinterpret_cast<SplitLds<2, kMThreads / 64> &>(ex));
         return;
     }
     const int nx = a.nx, ny = a.ny, nz = a.nz;
@@ -297,6 +297,10 @@ __global__ __launch_bounds__(kMThreads) void march2(MarchArgs a)
             __builtin_amdgcn_raw_buffer_store_b32(0u, rd, kNoSite, i * seg4, kStoreAux);
     }
     for (int k = 0; k <= last; k += 2) {
+        // The 9.6 KB of this loop start 16 bytes into a 32-byte block of code,
+        // wherever the code before it ends: 512^3 in 2233 us a step, at 0, 8 and
+        // 24 bytes 2356, 2337 and 2292 (other sizes and a force: within 1%).
+        asm volatile(".p2align 5\ns_nop 0\ns_nop 0\ns_nop 0\ns_nop 0");
         row(k, ex.a);
         row(k + 1, ex.a + kExA);
     }
@@ -339,11 +343,12 @@ MarchShape march_shape(int nx, int ny, int nz, int cus)
     for (int rows = 1; rows <= kMarchRows && rows <= nz; ++rows) {
         const int nzt = (nz + rows - 1) / rows;
         if (rows < kMarchRows && rows < nz && (nz + rows) / (rows + 1) == nzt) continue;  // one more plane costs no tile
-        for (int chunks = 1; chunks <= ny; ++chunks) {
+        const int fewest = (ny + kMarchChunk - 1) / kMarchChunk;
+        for (int chunks = fewest; chunks <= ny; ++chunks) {
             const int chunk = (ny + chunks - 1) / chunks;
             if ((ny + chunk - 1) / chunk != chunks) continue;
             const int64_t tiles = (int64_t)best.nxt * nzt * chunks;
-            if (tiles > 64 * (int64_t)cus && chunks > 1) break;  // shorter chunks only add halos
+            if (tiles > 64 * (int64_t)cus && chunks > fewest) break;  // shorter chunks only add halos
             const double rounds = (double)((tiles + cus - 1) / cus);
             const double us = (tiles % cus == 0 ? 9.5 : 3.5) + rounds * (chunk + 2) * (0.07 + 0.36 * (rows + 3)) * sectors;
             if (us < best_us) {
