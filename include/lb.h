@@ -156,11 +156,12 @@ int lb_step(lb_lattice *lat, int n);
  * array of the library, 16 MiB + 128 KiB per device, held until the process
  * ends; each step is an ordinary kernel launch on the lattice stream (no
  * graph is built, so a caller may capture the call into its own).
- * Limit: 64 bytes per step workgroup plus 256 + 64 per 256 workgroups, in
+ * Limit: 64 bytes per step workgroup plus 256 + 32 per 256 workgroups, in
  * half of the array; lattices whose totals are split (FP32 without solids,
- * where two-step launches pay) take twice of both; a
- * 512^3 lattice at 4 sites per lane (131072 workgroups) fits, lattices that
- * need more are rejected with LB_EINVAL and the sizes in lb_last_error().  All calls on one device
+ * where two-step launches pay) take twice of both, and run one step per
+ * launch where two steps' partials do not fit.  A 512^3 lattice at 4 sites
+ * per lane (131072 workgroups) fits; lattices that need more are rejected with
+ * LB_EINVAL and the sizes in lb_last_error().  All calls on one device
  * share the one array, which keeps the last call's contents: calls that
  * overlap on one device (other streams, other threads) race and must not be
  * issued.  Call with the lattice's device current.

@@ -239,13 +239,18 @@ int total_parts_of(const lb_lattice *h)
 
 int max_total_parts(const lb_lattice *h) { return h->split.m1 != 0.0 ? 8 : 4; }
 
-// Scratch layout for lattice h and runs of parts partials per buffer: ticket
-// (one 256-byte slot), the reduce workgroups' partials (4 doubles each, split totals: 8; rounded up to 256 bytes),
-// then two buffers of as many doubles per partial.
+// The partials (one per tile and plane) of each step of a two-step launch.
+int march_parts(const lb_lattice *h) { return h->march.nxt * h->march.nyt * h->nz; }
+
+// Scratch layout for lattice h and runs of parts partials per buffer: tickets
+// (one 256-byte slot), the reduce workgroups' partials of the last launch's one
+// or two steps (4 doubles each, split totals: 8; rounded up to 256 bytes), then
+// two buffers of as many doubles per partial.
 size_t scratch_gpart_bytes(const lb_lattice *h, size_t parts)
 {
-    const size_t ngroups = (parts + kRedChunk - 1) / kRedChunk;
-    return (ngroups * 2 * max_total_parts(h) * sizeof(double) + 255) & ~(size_t)255;
+    const size_t one = ((size_t)h->grid + kRedChunk - 1) / kRedChunk, march = (size_t)march_parts(h);
+    const size_t two = h->march.use && parts >= 2 * march ? 2 * ((march + kRedChunk - 1) / kRedChunk) : 0;
+    return (std::max(one, two) * max_total_parts(h) * sizeof(double) + 255) & ~(size_t)255;
 }
 
 size_t scratch_need(const lb_lattice *h, size_t parts)
@@ -267,11 +272,8 @@ TotalsBufs scratch_bufs(const lb_lattice *h, unsigned char *base, size_t parts)
     return tb;
 }
 
-// The partials (one per tile and plane) of each step of a two-step launch, the
-// partials that one buffer of a run holds, and whether runs with the buffers
-// tb take two steps per launch.
-int march_parts(const lb_lattice *h) { return h->march.nxt * h->march.nyt * h->nz; }
-
+// The partials that one buffer of a run holds, and whether runs with the
+// buffers tb take two steps per launch.
 size_t buf_parts(const lb_lattice *h)
 {
     return std::max((size_t)h->grid, h->march.use ? 2 * (size_t)march_parts(h) : (size_t)0);
