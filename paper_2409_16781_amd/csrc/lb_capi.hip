@@ -1461,6 +1461,8 @@ int lb_tune(lb_lattice *h, int reps)
     Events evs(2);
     HIP_OR_FAIL(evs.create());
     const int saved_variant = h->variant, saved_order = h->tile_order, saved_nt = h->pull_nt;
+    const int saved_auto = h->auto_variant;
+    h->auto_variant = 0;  // as after the choice: the kernels that are timed are those that will run
     int rc = LB_OK;
     // two passes over the candidates, each keeping its faster timing (drift
     // of the clocks during the sweep then favours no candidate)
@@ -1501,12 +1503,14 @@ int lb_tune(lb_lattice *h, int reps)
     h->variant = saved_variant;
     h->tile_order = saved_order;
     h->pull_nt = saved_nt;
-    if (rc != LB_OK) return rc;
+    if (rc != LB_OK) {
+        h->auto_variant = saved_auto;
+        return rc;
+    }
     const Cand *best = &cands[0];
     for (const Cand &c : cands)
         if (c.ms < best->ms) best = &c;
     h->variant = best->variant;
-    h->auto_variant = 0;
     h->vsites = sites_per_thread(h->codec, best->variant);
     h->tile_order = best->order;
     h->pull_nt = best->nt;

@@ -569,6 +569,7 @@ void *pick_step(int codec, int variant, bool solids, bool macros, bool ffield, b
                 bool rest_once = false)
 {
     if (rest_once && codec == kF16 && variant == 3) {
+        if (solids && !macros && pull_nt) return reinterpret_cast<void *>(&step_vec<kF16, 1, true, false, 4, false, true, true>);
         if (solids)
             return macros ? reinterpret_cast<void *>(&step_vec<kF16, 1, true, true, 4, false, false, true>)
                           : reinterpret_cast<void *>(&step_vec<kF16, 1, true, false, 4, false, false, true>);
