@@ -1451,15 +1451,15 @@ int lb_tune(lb_lattice *h, int reps)
     // of the previous launch (the append's cost grows with the grid) -- into
     // a ring and counter of the tuner's own: the state, the step count and
     // the lattice's totals stay as they are
+    Events evs(2);
+    HIP_OR_FAIL(evs.create());
     double *tring = nullptr;
     unsigned long long *tctr = nullptr;
-    if (hipMalloc(&tring, 64 * 4 * sizeof(double)) != hipSuccess ||
+    if (hipMalloc(&tring, (size_t)kRingCap * 4 * sizeof(double)) != hipSuccess ||
         hipMalloc(&tctr, sizeof(unsigned long long)) != hipSuccess) {
         if (tring) (void)hipFree(tring);
         return fail(LB_ENOMEM, "hipMalloc(tuner totals)");
     }
-    Events evs(2);
-    HIP_OR_FAIL(evs.create());
     const int saved_variant = h->variant, saved_order = h->tile_order, saved_nt = h->pull_nt;
     const int saved_auto = h->auto_variant;
     h->auto_variant = 0;  // as after the choice: the kernels that are timed are those that will run
