@@ -91,6 +91,7 @@ struct lb_lattice {
     double n_fluid;
     double *partials;
     double *gpartials;
+    size_t parts_held; // partials that one of the two buffers has room for
     TotalSplit split;  // of split totals (total_split), or zeros
     unsigned int *ticket;
     double *ring;
@@ -593,29 +594,47 @@ int enqueue_steps(lb_lattice *h, int n, float *rho, float *u)
     return LB_OK;
 }
 
-// The buffers of the per-step totals for runs of parts partials per launch:
-// two buffers of them, and one slot per reduce workgroup for two steps.
+// The buffers of the per-step totals for runs of parts partials per launch, if
+// those held are smaller: two buffers of them, and one slot per reduce
+// workgroup for two steps.  On failure the lattice keeps the ones it has.
 int alloc_partials(lb_lattice *h, size_t parts)
 {
-    if (h->partials) (void)hipFree(h->partials);
-    if (h->gpartials) (void)hipFree(h->gpartials);
-    h->partials = h->gpartials = nullptr;
+    if (parts <= h->parts_held) return LB_OK;
     const size_t nc = max_total_parts(h), ngroups = (parts + kRedChunk - 1) / kRedChunk;
-    if (hipMalloc(&h->partials, parts * 2 * nc * sizeof(double)) != hipSuccess ||
-        hipMalloc(&h->gpartials, ngroups * 2 * nc * sizeof(double)) != hipSuccess)
+    double *p = nullptr, *g = nullptr;
+    if (hipMalloc(&p, parts * 2 * nc * sizeof(double)) != hipSuccess ||
+        hipMalloc(&g, ngroups * 2 * nc * sizeof(double)) != hipSuccess) {
+        if (p) (void)hipFree(p);
         return fail(LB_ENOMEM, "hipMalloc(partials)");
+    }
+    if (h->partials) {
+        const hipError_t e = hipStreamSynchronize(h->stream);
+        if (e != hipSuccess) {
+            (void)hipFree(p);
+            (void)hipFree(g);
+            return fail(LB_EHIP, "hipStreamSynchronize: %s", hipGetErrorString(e));
+        }
+        (void)hipFree(h->partials);
+        (void)hipFree(h->gpartials);
+        h->graphs.invalidate();  // they hold the old addresses
+    }
+    h->partials = p;
+    h->gpartials = g;
+    h->parts_held = parts;
     return LB_OK;
 }
 
-// Step kernel of another vector width (the stream's work is waited for).
+// Step kernel of another vector width.
 int set_variant(lb_lattice *h, int variant)
 {
     if (variant == h->variant) return LB_OK;
-    HIP_OR_FAIL(hipStreamSynchronize(h->stream));
+    const int vsites = sites_per_thread(h->codec, variant);
+    const int grid = (int)std::min<uint64_t>((h->n / vsites + kBlock - 1) / kBlock, 0x7fffffffull);
+    if (int rc = alloc_partials(h, std::max(buf_parts(h), (size_t)grid))) return rc;
     h->variant = variant;
-    h->vsites = sites_per_thread(h->codec, variant);
-    h->grid = (int)std::min<uint64_t>((h->n / h->vsites + kBlock - 1) / kBlock, 0x7fffffffull);
-    return alloc_partials(h, buf_parts(h));
+    h->vsites = vsites;
+    h->grid = grid;
+    return LB_OK;
 }
 
 void release(lb_lattice *h)
@@ -1442,10 +1461,7 @@ int lb_tune(lb_lattice *h, int reps)
     }
     if (cands.empty()) return LB_OK;  // only the one-site kernel fits this nx
     // partials for the largest grid (timing launches, and the choice)
-    if (max_grid > h->grid) {
-        HIP_OR_FAIL(hipStreamSynchronize(h->stream));
-        if (int rc = alloc_partials(h, std::max((size_t)max_grid, buf_parts(h)))) return rc;
-    }
+    if (int rc = alloc_partials(h, std::max((size_t)max_grid, buf_parts(h)))) return rc;
     // every timing launch reads the current state and writes the other array,
     // and, like a step inside a run, its first workgroup appends the totals
     // of the previous launch (the append's cost grows with the grid) -- into

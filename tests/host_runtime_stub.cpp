@@ -198,10 +198,45 @@ static void tuner_ring()
     lb_destroy(h);
 }
 
+// Setting or clearing a force field changes the step kernel's width, and with
+// it the number of partials: when memory runs out in between, the lattice
+// steps on with buffers that exist.
+static void force_field_memory()
+{
+    lb_lattice *h = make(32, 16, 12, LB_F32, true);
+    void *fx = nullptr;
+    (void)hipMalloc(&fx, 32 * 16 * 12 * sizeof(float));
+    expect(lb_step(h, 70) == LB_OK, "step");
+    g_allow = 1;  // the field itself
+    (void)lb_set_force_field(h, static_cast<float *>(fx));
+    expect(lb_step(h, 70) == LB_OK && lb_step(h, 1) == LB_OK, "step with the field");
+    g_allow = 0;
+    expect(lb_set_force_field(h, nullptr) == LB_OK, "clearing the field needs no memory");
+    expect(lb_step(h, 70) == LB_OK && lb_step(h, 1) == LB_OK, "step without the field");
+    lb_destroy(h);
+}
+
+// A sweep that finds no memory for its widest grid leaves the lattice, and its
+// captured runs, as they were.
+static void tuner_memory()
+{
+    lb_lattice *h = make(128, 256, 256, LB_F32, true);
+    expect(lb_step(h, 64) == LB_OK, "step");
+    for (int allow = 0; allow < 4; ++allow) {
+        g_allow = allow;
+        (void)lb_tune(h, 2);
+        g_allow = -1;
+        expect(lb_step(h, 64) == LB_OK && lb_step(h, 1) == LB_OK, "step after a failed sweep");
+    }
+    lb_destroy(h);
+}
+
 int main(int argc, char **argv)
 {
     const std::string which = argc > 1 ? argv[1] : "";
     if (which == "tuner_ring") tuner_ring();
+    else if (which == "force_field_memory") force_field_memory();
+    else if (which == "tuner_memory") tuner_memory();
     else {
         std::printf("unknown case %s\n", which.c_str());
         return 2;

@@ -25,7 +25,7 @@ def stub(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["tuner_ring"])
+@pytest.mark.parametrize("case", ["tuner_ring", "force_field_memory", "tuner_memory"])
 def test_buffers_of_every_launch(stub, case):
     res = subprocess.run([stub, case], capture_output=True, text=True, timeout=60)
     assert res.returncode == 0 and res.stdout.startswith("ok"), res.stdout + res.stderr
