@@ -1061,9 +1061,8 @@ int lb_set_force_field(lb_lattice *h, const float *fx)
     }
     HIP_OR_FAIL(hipMemcpyAsync(h->ffield, fx, h->n * sizeof(float), hipMemcpyDeviceToDevice, h->stream));
     // the field is read as whole vectors of the row kernels: any nx works with
-    // one site per lane.  A lattice of default width takes the widest vectors:
-    // the one-site kernels with and without field output round j.u in another
-    // order, and a gradient must not depend on its checkpoints.
+    // one site per lane.  A lattice of default width takes the widest vectors
+    // (default_variant was fitted without fields).
     int v = h->variant == 0 ? 3 : h->variant;
     if (h->auto_variant != 0)
         for (v = 1; h->nx % sites_per_thread(h->codec, v) != 0;) ++v;

@@ -483,9 +483,9 @@ __device__ __forceinline__ void relax_pair_field(float &gi, float &gj, float s, 
 // spends 25 of its 190 instructions a site on these terms, 18 of them moves
 // of the per-direction constants from scalar registers.)
 // kField 1, 2: the x-force of this site is fx (the uniform one plus the
-// field's).  2 sums j.u and u.F from x on, 1 (and 0) from y on, the order that
-// each force-field kernel has had (an outlet flux is compared to 1e-9, and
-// another order moves it by 1e-8).
+// field's).  2 (lattices without solids) sums j.u and u.F from x on, 1 (and 0)
+// from y on, the orders that their force-field kernels have had (an outlet
+// flux is compared to 1e-9, and another order moves it by 1e-8).
 template <bool kForce = true, int kField = 0>
 __device__ __forceinline__ void collide(float (&g)[kQ], const Coll &p, float &rho, float &ux, float &uy, float &uz,
                                         float fx = 0.0f)
@@ -1587,7 +1587,9 @@ __device__ __forceinline__ void tile_update(const StepArgs &a, const char *src, 
     if constexpr (kFField) {
         load_masks<V>(reinterpret_cast<const uint32_t *>(a.fx_field) + g.s0, reinterpret_cast<uint32_t(&)[V]>(fxs));
     }
-    constexpr int kOrder = kSolids == (kMacros && NW == 1) ? 2 : 1;
+    // one order for every width, with and without field output: a gradient's
+    // recomputed steps write their moments and must be the forward ones
+    constexpr int kOrder = kSolids ? 1 : 2;
     collide_sites<C, NW, kFField ? kOrder : 0, kRestOnce>(d, cp, a.sc, rng, fxs, mr, mu, mv, mw);
 
     if (g.active) {
