@@ -1407,7 +1407,7 @@ long long lb_query(const lb_lattice *h, int key)
         case 10: return h->rescales;
         case 11: return h->tile_order;
         case 12: return h->pull_nt;
-        case 13: return h->march.use ? 2 : 1;
+        case 13: return run_pairs(h, own_bufs(h)) ? 2 : 1;
         default: return -1;
     }
 }
