@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kBlock) void reduce_domains(BatchTotalsArgs a)
     const int d = blockIdx.x;
     const unsigned long long step = __hip_atomic_load(a.step_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     double tot[4];
-    block_sum<4>(a.partials + 4 * (size_t)a.doms[d].tile_begin, a.doms[d].ntiles, tot, false);
+    block_sum<4>(a.partials + 4 * (size_t)a.doms[d].tile_begin, a.doms[d].ntiles, tot);
     if (threadIdx.x == 0) {
         double *r = a.ring + 4 * ((size_t)d * kRingCap + step % kRingCap);
         r[0] = a.doms[d].n_fluid + tot[0];

@@ -760,7 +760,7 @@ __device__ __forceinline__ void store_block_totals(const double (&acc)[NC], doub
 
 // Sum v[0..count) (NC doubles each) in a fixed tree; the result is valid in thread 0.
 template <int NC>
-__device__ __forceinline__ void block_sum(const double *v, int count, double (&out)[NC], bool coherent)
+__device__ __forceinline__ void block_sum(const double *v, int count, double (&out)[NC])
 {
     __shared__ double tot[NC][kBlock];
     double s[NC];
@@ -769,7 +769,7 @@ __device__ __forceinline__ void block_sum(const double *v, int count, double (&o
     for (int b = threadIdx.x; b < count; b += kBlock) {
 #pragma unroll
         for (int k = 0; k < NC; ++k)
-            s[k] += coherent ? __hip_atomic_load(&v[NC * b + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : v[NC * b + k];
+            s[k] += v[NC * b + k];
     }
 #pragma unroll
     for (int k = 0; k < NC; ++k) tot[k][threadIdx.x] = s[k];

@@ -286,8 +286,6 @@ struct March2Shape {
     double us;                // estimated time of a launch
 };
 
-// The reduction of one step's partials into the ring of per-step totals.
-
 struct InitArgs {
     void *dst;
     Layout lay;

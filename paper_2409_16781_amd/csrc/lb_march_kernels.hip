@@ -15,10 +15,11 @@
 //    values: those with c_y = -1 belong to the second step of row y - 1, which
 //    is complete now and is collided and stored; those with c_y = 0 wait one
 //    row and those with c_y = +1 two rows, in registers.
-//  - The exchange buffer is double (2 x 62 KiB of the CU's 160 KiB), so one
-//    barrier a row is enough.  1024 threads at 128 VGPRs: 16 waves a CU, the
-//    largest region the register file holds (19 values in flight, 19 waiting
-//    and the collision's temporaries per site).
+//  - The exchange buffers hold two rows of the twelve populations that are
+//    read in their own row and four rows of the other four (154.7 KiB of the
+//    CU's 160), so one barrier a row is enough.  1024 threads at 128 VGPRs: 16
+//    waves a CU, the largest region the register file holds (19 values in
+//    flight, 19 waiting and the collision's temporaries per site).
 //  - The loads of the next row are issued between the first step and the
 //    barrier and land during the second step.  Lanes and rows without a site
 //    load and store through descriptors (or offsets) out of range, which move
@@ -72,7 +73,6 @@ struct Exchange {
     float a[2 * kExA], p[4 * kExP];
 };
 
-constexpr bool exchanged(int i) { return kSlot[i] >= 0; }
 // Offsets from the site's own slot minus one plane and one column: of the own
 // value of population i, and of the value it brings from its neighbour.
 constexpr int own_at(int i) { return kSlot[i] * kMPlane + kMRS + 1; }
