@@ -7,8 +7,9 @@ tau = 0.55, no body force; populations stored as FP32, FP16, BF16 or scaled
 16-bit fixed point (shifted by the lattice weights), FP32 arithmetic, FP64
 conservation totals every step.
 A step is one fused update of all 134,217,728 sites with the inputs already
-resident in HBM; the library takes two FP32 steps per launch, and the roofline
-record is that of the one-step kernel timed alone.
+resident in HBM; the library takes two FP32 steps per launch.  The roofline
+record is that of the one-step kernel timed alone, timed_path that of the
+launches behind ``value``.
 
 Prints one JSON line: MLUPS of the FP32-storage path as ``value``, the
 16-bit-storage results beside it, each codec's error against stored FP64
@@ -64,12 +65,12 @@ def workload_fields(n):
     return cfg
 
 
-STEP_KERNEL_SOURCES = ("lb_internal.h", "lb_device.h", "lb_kernels.hip")
+STEP_KERNEL_SOURCES = ("lb_internal.h", "lb_device.h", "lb_kernels.hip", "lb_march_kernels.hip")
 
 
 def step_kernel_digest(root):
     """SHA-256 over the code (comments and whitespace removed) of the sources
-    the single-lattice step kernel is built from."""
+    the single-lattice step kernels are built from."""
     import hashlib
     import re
     h = hashlib.sha256()
@@ -82,10 +83,10 @@ def step_kernel_digest(root):
 
 
 def measured_traffic(codec, n):
-    """HBM bytes per step-kernel launch from the committed rocprofv3 counters
-    (FETCH_SIZE and WRITE_SIZE, each scaled by what it reads for a copy of
-    known size), or None when the kernel source changed since they were taken
-    or the lattice differs."""
+    """HBM bytes per step-kernel launch (codec "f32_two_steps": per launch of two
+    steps) from the committed rocprofv3 counters (FETCH_SIZE and WRITE_SIZE,
+    each scaled by what it reads for a copy of known size), or None when the
+    kernel source changed since they were taken or the lattice differs."""
     here = os.path.dirname(os.path.abspath(__file__))
     path = os.path.join(here, "profiles", "step_vec_512cube_tgv.traffic.json")
     try:
@@ -157,7 +158,7 @@ def run_codec(torch, lbm, cfg, codec, steps, warmup, reps):
                step_kernel_ms=kernel_ms, achieved_gbs=gbs, frac_hbm=gbs / HBM_PEAK_GBS, copy_gbs=copy_gbs,
                frac_copy=gbs / copy_gbs, mass_drift_per_step=drift / max(1, len(sums) - 1),
                variant=lat.info["variant"], sites_per_thread=lat.info["sites_per_thread"],
-               grid=lat.info["grid"], steps_done=lat.steps_done)
+               grid=lat.info["grid"], steps_per_launch=lat.query(13), steps_done=lat.steps_done)
     if codec == "s16":
         res["exponents"] = [int(e) for e in lat.get_scales()]
         res["widenings_warmup"] = widen0
@@ -165,6 +166,20 @@ def run_codec(torch, lbm, cfg, codec, steps, warmup, reps):
         res["widenings_timed"] = lat.info["rescales"] - widen0
     lat.close()
     return res, u_out
+
+
+def timed_path(m, codec, n):
+    """What the launches behind a codec's MLUPS move per step: measured bytes
+    (None without counters of the present kernels) over the timed wall clock."""
+    k = m["steps_per_launch"]
+    per_launch = measured_traffic(codec if k == 1 else f"{codec}_two_steps", n)
+    out = dict(kernel="step_vec" if k == 1 else "march2", steps_per_launch=k, ms_per_step=round(m["ms_per_step"], 4),
+               sweep_bytes_per_step=bytes_per_site(codec) * n ** 3, traffic_bytes_per_step=None)
+    if per_launch is not None:
+        gbs = per_launch / k / (m["ms_per_step"] * 1e-3) / 1e9
+        out.update(traffic_bytes_per_step=round(per_launch / k), traffic_gbs=round(gbs, 1),
+                   frac_hbm=round(gbs / HBM_PEAK_GBS, 4), frac_of_copy=round(gbs / m["copy_gbs"], 4))
+    return out
 
 
 def run_batch(torch, lbm, steps, reps):
@@ -311,16 +326,17 @@ def run_small(torch, lbm, reps, steps=0):
             ms = sorted(times)[reps // 2]
             kernel_ms = lat.time_step_kernel(50)
             sums = lat.sums(1)
+            per_launch = lat.query(13)
             lat.close()
             nf = entry.get("fluid_sites", n)  # algorithmic bytes: fluid sites only
             kgbs = bytes_per_site(codec) * nf / (kernel_ms * 1e-3) / 1e9
             gbs = bytes_per_site(codec) * nf * cfg["steps"] / (ms * 1e-3) / 1e9
-            # kernel_ms: HIP events around single eagerly launched kernels,
-            # which on steps of tens of microseconds include a few
+            # kernel_ms: HIP events around single eagerly launched one-step
+            # kernels (runs may take two steps a launch), which on steps of tens of microseconds include a few
             # microseconds of launch; the step rate of the captured run
             # (gbs_algorithmic, frac_hbm) carries no such overhead
             entry[codec] = dict(mlups=round(n * cfg["steps"] / (ms * 1e-3) / 1e6, 1),
-                                ms_per_step=round(ms / cfg["steps"], 5),
+                                ms_per_step=round(ms / cfg["steps"], 5), steps_per_launch=per_launch,
                                 gbs_algorithmic=round(gbs, 1), frac_hbm=round(gbs / HBM_PEAK_GBS, 4),
                                 kernel_ms=round(kernel_ms, 5), kernel_gbs=round(kgbs, 1),
                                 kernel_frac_hbm=round(kgbs / HBM_PEAK_GBS, 4),
@@ -470,6 +486,7 @@ def main():
                      "bytes_per_site": bytes_per_site(main_codec), "kernel_ms": round(m["step_kernel_ms"], 4),
                      "kernel": "step_vec (fused pull-stream + BGK/Guo collide)",
                      "copy_ceiling_gbs": round(m["copy_gbs"], 1), "frac_of_copy": round(m["frac_copy"], 4)},
+        "timed_path": timed_path(m, main_codec, n),
         "variants": {c: {k: (round(v, 6) if isinstance(v, float) else v) for k, v in r.items()}
                      for c, r in results.items()},
     }
