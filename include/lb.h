@@ -197,7 +197,10 @@ int lb_macros(lb_lattice *lat, float *rho, float *u);
  * stored): the moments of Section 2 summed over the lattice, which the
  * collision of Eq. 1 conserves (mass exactly, momentum up to the force F per
  * fluid site and step).  Every stored value is converted to FP64 and summed
- * in FP64 on the GPU in a fixed order (bitwise reproducible).  k must be <= min(steps taken since lb_init_eq, 4096).
+ * in FP64 on the GPU in a fixed order (bitwise reproducible).  FP32 lattices
+ * that take two steps a launch (and the same in one array) round each site's
+ * moments to multiples of 2^-85 (up to 128^3), 2^-79 (512^3) or 2^-75 at most,
+ * so that a run gives the same bits however it is cut into calls.  k must be <= min(steps taken since lb_init_eq, 4096).
  * Synchronises the stream.  Returns LB_EUNSTABLE when any copied value is
  * NaN or infinite (the values are still copied).
  */
@@ -469,7 +472,8 @@ int lb2d_step(lb2d_lattice *lat, int n);
 /* rho = sum f and u = sum c f / rho of the stored state into DEVICE rho (N) and u (2N); solid sites 0. */
 int lb2d_macros(lb2d_lattice *lat, float *rho, float *u);
 
-/* FP64 {mass, momentum x, y} of the fluid sites after each of the last k steps (out: 3k doubles). */
+/* FP64 {mass, momentum x, y} of the fluid sites after each of the last k steps (out: 3k doubles).
+ * Each pair of sites' moments is rounded to a multiple of 2^-73 or finer (see lb_sums). */
 int lb2d_sums(lb2d_lattice *lat, double *out, int k);
 
 /* Raw state: 9 planes of N floats (g = f - w), host or device (where). */

@@ -673,7 +673,8 @@ void release(lb_lattice *h)
 //             / 7.9, 256^3 204 / 200 / 207; solids 64^3 32 / 28 / 24, 256^3 947
 //             / 1005 / 1093
 // The upper bounds also keep the totals of every lattice that fits with
-// 16-byte vectors (scaled: 8-byte) within the scratch array of lb_step_noalloc.
+// 16-byte vectors (scaled: 8-byte) within the scratch array of lb_step_noalloc;
+// in FP16 that costs 512^3 the narrower vectors' 6%.
 int default_variant(int storage, bool inplace, bool solids, uint64_t n)
 {
     auto by_size = [n](int lg3, int lg2) { return n <= (1ull << lg3) ? 3 : (n <= (1ull << lg2) ? 2 : 1); };
@@ -827,10 +828,11 @@ int create_impl(lb_lattice **out, int nx, int ny, int nz, double tau, const uint
     // Two steps per launch for FP32 lattices in two arrays, where the launch
     // shape says it pays (LB_TWO_STEP=0: never, 2: always).  Not with solids
     // (the masks' address selections and the second step's choice between own
-    // and neighbours' values cost more than the saved traffic: 256x128x128
-    // channel 102 us a step in one-step launches, 113 in pairs; 128^3 sphere
-    // 63 and 59) nor, as long as one is set, with a force field (128^3: 57 and
-    // 63, with solids 64 and 83).
+    // and neighbours' values: 256x128x128 channel 102 us a step in one-step
+    // launches, 113 in pairs; 128^3 sphere 63 and 59) nor, as long as one is set,
+    // with a force field (128^3: 57 and 63, with solids 64 and 83).  Those pairs
+    // were timed before march_shape chose the tile: the channel's extents
+    // without solids took 100 us in them and take 81 now.
     // Their totals are split into parts whose sums do not depend on how a run
     // is cut into launches, and so are those of the same lattice in one array.
     const long two = env_long("LB_TWO_STEP", 1);

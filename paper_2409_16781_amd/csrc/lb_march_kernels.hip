@@ -33,15 +33,16 @@
 // add_moments' order-independent totals): the state and the per-step totals
 // are the same bits.
 //
-// Measured on MI355X, FP32, microseconds a step with its totals, two step_vec
-// launches -> one march2 launch: 512^3 3200 -> 2150, 256^3 400 -> 293, 128^3
-// 56.5 -> 44.5, 64^3 11.6 -> 9.2, 32^3 7.5 -> 5.8.  What bounds it on large
-// lattices is memory: without the collisions it runs at the same speed (5.4
-// TB/s over 22-23 GB at 512^3, 10.2 of them stores), and issuing the loads
-// earlier (a whole row ahead) or deeper prefetch of the halo waves is slower.
-// On small ones it is the row of the march (0.36 us per wave of the region).  Marching along z puts consecutive rows of a wave 20 MB apart at
-// 512^3 and is 5% slower; one step per launch in this scheme loses to
-// step_vec (3.4-4.4 ms at 512^3).
+// Measured on MI355X, FP32, microseconds a step with its totals, step_vec (its
+// default width) -> march2: 512^3 3174 -> 2240, 256^3 400 -> 294, 96^3 27.3 ->
+// 23.3, 64^3 9.5 -> 8.9, 48^3 7.3 -> 6.4, 32^3 4.9 -> 5.7, 24^3 5.0 -> 4.7.
+// What bounds it on large lattices is memory: without the collisions it runs
+// at the same speed (4.9 TB/s over 21.9 GB a launch at 512^3, 10.2 of them
+// stores), and issuing the loads earlier (a whole row ahead) or deeper prefetch
+// of the halo waves is slower.  On small ones it is the row of the march (0.36
+// us per wave of the region).  Marching along z puts consecutive rows of a wave
+// 20 MB apart at 512^3 and is 5% slower; one step per launch in this scheme
+// loses to step_vec (3.4-4.4 ms at 512^3).
 #include <algorithm>
 
 #include "lb_device.h"
@@ -331,7 +332,10 @@ __global__ __launch_bounds__(kMThreads) void march2(MarchArgs a)
 // and store them in parts: little lost while the state fits the L2s, 1.25x in
 // the memory-side cache, 1.4x to 1.8x beyond (200^3: 440 us against 414 of two
 // one-step launches; 192^3: 260 against 361).  A one-step launch takes 6.3 us
-// and its bytes at 6.4 TB/s.
+// and its bytes at 6.4 TB/s: that is its time with 16-byte vectors.  With the
+// widths of default_variant the estimate is off by a little on both sides: it
+// keeps pairs at 32^3 (5.7 us a step against 4.9) and one step a launch at
+// 125^3 (55.0 against 51.8 in pairs) and 101x75x47 (15.4 against 14.4).
 MarchShape march_shape(int nx, int ny, int nz, int cus)
 {
     MarchShape best{};
