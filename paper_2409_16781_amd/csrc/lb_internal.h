@@ -104,8 +104,8 @@ constexpr int kRedChunk = 256;   // step-workgroup partials summed by one reduce
 struct TotalsArgs {
     const double *partials;   // nc doubles per step workgroup
     int nparts;               // step workgroups
-    int nc;                   // 4, or 8 where the moments are summed in two parts (FP32 lattices)
-    int e1, e2;               // of the two parts (TotalSplit)
+    short nc;                 // 4, or 8 where the moments are summed in two parts (FP32 lattices)
+    signed char e1, e2;       // of the two parts (TotalSplit)
     double *gpartials;        // nc doubles per reduce workgroup, for each step of a launch
     unsigned int *ticket;     // kTickets arrival counters, 0 between launches
     double *ring;             // kRingCap x 4 doubles
