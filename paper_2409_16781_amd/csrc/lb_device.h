@@ -1043,10 +1043,10 @@ __device__ __forceinline__ void append_prev_totals(int n, const TotalsArgs (&pre
 // small lattice the totals kernel and the gap before it (32x16x8, a step with
 // its fields: 10.2 -> 8.0 us a call); each workgroup's release fence makes
 // it slow for many (kFinishGroups).  Not for scaled storage, whose flag must
-// be complete first.  The step counter is loaded where it is used: a load whose
-// result a way out leaves unused makes every wave wait for its own stores, also
-// in launches that do not come here (f16, 48x40x24 with solids, 50 steps with
-// the load ahead of the sum: 10.95 us a step; 10.83).
+// be complete first.  The step counter is loaded ahead of the sum (one latency
+// less: 8.25 -> 8.09 us) and waited for here: left to the compiler, lanes that
+// do not use it have every wave of every launch wait for its own stores (f16
+// 48x40x24 with solids, 50 steps: 10.95 us a step; 10.83).
 template <int NC>
 __device__ __forceinline__ void finish_totals(const TotalsArgs &t)
 {
@@ -1056,25 +1056,20 @@ __device__ __forceinline__ void finish_totals(const TotalsArgs &t)
     if (threadIdx.x == 0) arrived = atomicAdd(&t.ticket[0], 1u);
     if (__builtin_amdgcn_readfirstlane(arrived) != (unsigned int)t.nparts - 1) return;
     __threadfence();
+    const unsigned long long step = __hip_atomic_load(t.step_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if constexpr (NC == 8) {
         const SplitSum s = wave_split(sum_split(t, 0, t.nparts, 16, true));
-        if (threadIdx.x < 4) {
-            const unsigned long long step = __hip_atomic_load(t.step_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            store_split(t, step, s);
-            if (threadIdx.x == 0) {
-                __hip_atomic_store(&t.ticket[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(t.step_counter, step + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+        if (threadIdx.x < 4) store_split(t, step, s);
     } else {
         double tot[NC];
         wave_sum<NC>(t.partials, t.nparts, tot, true);
-        if (threadIdx.x != 0) return;
-        const unsigned long long step = __hip_atomic_load(t.step_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        store_ring(t, step, tot);
-        __hip_atomic_store(&t.ticket[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(t.step_counter, step + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+        if (threadIdx.x == 0) store_ring(t, step, tot);
     }
+    if (threadIdx.x != 0) return;
+    __hip_atomic_store(&t.ticket[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(t.step_counter, step + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ------------------------------------------------ step: vector-row kernel --
