@@ -292,8 +292,8 @@ TotalsArgs totals_args(const lb_lattice *h, const double *partials, int nparts, 
     TotalsArgs t{};
     t.ovf = h->codec == kS16 ? h->ovf + par : nullptr;
     t.nc = total_parts_of(h);
-    t.e1 = h->split.e1;
-    t.e2 = h->split.e2;
+    t.e1 = quantum_exponent(h->split.m1);
+    t.e2 = quantum_exponent(h->split.m2);
     t.partials = partials;
     t.nparts = nparts;
     t.gpartials = tb.gpartials;

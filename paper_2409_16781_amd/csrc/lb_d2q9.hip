@@ -98,8 +98,8 @@ TotalsArgs totals2(const lb2d_lattice *h, const double *partials, int nparts)
 {
     TotalsArgs t{};
     t.nc = 8;
-    t.e1 = h->split.e1;
-    t.e2 = h->split.e2;
+    t.e1 = quantum_exponent(h->split.m1);
+    t.e2 = quantum_exponent(h->split.m2);
     t.partials = partials;
     t.nparts = nparts;
     t.gpartials = h->gpartials;

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <cmath>
 #include <stdint.h>
 
 namespace lbm {
@@ -27,8 +28,9 @@ struct Scale16 {
 // quanta 2^e1 and 2^e2.
 struct TotalSplit {
     double m1, m2;
-    int e1, e2;
 };
+// e1 of m1, e2 of m2.
+inline signed char quantum_exponent(double m) { return (signed char)(m != 0.0 ? std::ilogb(m) - 52 : 0); }
 
 TotalSplit total_split(uint64_t group);
 
@@ -105,7 +107,7 @@ struct TotalsArgs {
     const double *partials;   // nc doubles per step workgroup
     int nparts;               // step workgroups
     short nc;                 // 4, or 8 where the moments are summed in two parts (FP32 lattices)
-    signed char e1, e2;       // of the two parts (TotalSplit)
+    signed char e1, e2;       // of the two parts (quantum_exponent)
     double *gpartials;        // nc doubles per reduce workgroup, for each step of a launch
     unsigned int *ticket;     // kTickets arrival counters, 0 between launches
     double *ring;             // kRingCap x 4 doubles

@@ -640,7 +640,7 @@ TotalSplit total_split(uint64_t group)
     int lg = 10;
     while ((1ull << lg) < group) ++lg;
     const int e1 = lg + 2 - 53, e2 = (e1 - 1) + lg - 53;
-    return TotalSplit{std::ldexp(1.5, 52 + e1), std::ldexp(1.5, 52 + e2), e1, e2};
+    return TotalSplit{std::ldexp(1.5, 52 + e1), std::ldexp(1.5, 52 + e2)};
 }
 
 int sites_per_thread(int codec, int variant)
